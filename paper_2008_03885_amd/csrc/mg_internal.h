@@ -281,6 +281,34 @@ template <typename T>
 hipError_t launch_tail(int dim, int G, const TailArgs &args, size_t lds_bytes, hipStream_t s,
                        int slots = 1);
 
+// The 2D tail of the levels 65^2, 33^2, 17^2 and 9^2 (tail2d.hip): compile-time sides, the
+// top level one of 65, 33, 17, the coarsest 9^2 by its dense inverse.
+constexpr int kTail2dCoarse = 9;
+template <typename T>
+struct Tail2dOp {
+  T a[3], b[4];  // separable levels: the symmetric 1D factors, a at 1..3 and b at 0..3
+  T w1, w2;      // cross weights
+  T om;          // omega / centre coefficient
+  int cross;
+};
+template <typename T>
+struct Tail2dArgs {
+  Tail2dOp<T> op[3];  // the 65^2, 33^2 and 17^2 levels (those above the top are not read)
+  int gamma, nu1, nu2, prolong, rb;
+  int zero_init, repeats;  // as TailArgs
+  const double *ainv_t;    // 9^2 inverse, transposed, 49 x 49
+  const void *f_top;
+  void *u_top;
+  const int *done;
+};
+template <typename T>
+size_t tail2d_lds_bytes(int top, bool sep);
+template <typename T>
+hipError_t tail2d_prepare(int top, bool sep);
+// sep: some level of the tail is not the radius-2 cross.
+template <typename T>
+hipError_t launch_tail2d(int top, const Tail2dArgs<T> &args, bool sep, hipStream_t s, int slots = 1);
+
 // The 3D tail of line passes (tail3d.hip): a 17^3 level whose operator is given by its 1D
 // factors, and the 9^3 coarsest level solved by sine transforms.
 constexpr int kTail3Side = 17, kTail3Coarse = 9;

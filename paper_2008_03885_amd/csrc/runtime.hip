@@ -363,6 +363,7 @@ struct mg_ctx {
   int tail_top = 0;        // first level handled by the LDS-resident tail (L: none)
   size_t tail_lds = 0;     // dynamic LDS bytes of the tail
   bool tail3 = false;      // 3D: the tail is 17^3 + 9^3 in the line-pass kernel
+  bool tail2d = false;     // 2D: the tail is a suffix of 65^2, 33^2, 17^2, 9^2 (tail2d.hip)
   int *eoff = nullptr;     // stencil entry lists of every level (tail kernel)
   double *ecoef = nullptr;
   std::vector<int> ent_begin, ent_count;
@@ -481,6 +482,35 @@ hipError_t launch_tail_at(mg_ctx *c, int l, T *u, const T *f, bool zero_u, const
     a.u_top = u;
     a.done = done;
     return mgk::launch_tail3<T>(a, s, c->slots);
+  }
+  if (c->tail2d && l < c->L - 1) {
+    mgk::Tail2dArgs<T> a{};
+    bool sep = false;
+    for (int k = l; k < c->L - 1; ++k) {
+      const LevelOp &op = c->ops[k];
+      mgk::Tail2dOp<T> &o = a.op[c->ns[k] == 65 ? 0 : c->ns[k] == 33 ? 1 : 2];
+      for (int i = 0; i < 4; ++i) {
+        if (i > 0) o.a[i - 1] = (T)op.a[3 + i];
+        o.b[i] = (T)op.b[3 + i];
+      }
+      o.w1 = (T)(-op.a[2]);
+      o.w2 = (T)(-op.a[1]);
+      o.om = (T)(c->omega / op.diag);
+      o.cross = op.cross ? 1 : 0;
+      sep = sep || !op.cross;
+    }
+    a.gamma = c->cfg.gamma;
+    a.nu1 = c->cfg.nu1;
+    a.nu2 = c->cfg.nu2;
+    a.prolong = c->cfg.prolong;
+    a.rb = c->cfg.smoother == MG_SMOOTH_RBJ ? 1 : 0;
+    a.zero_init = zero_u ? 1 : 0;
+    a.repeats = repeats;
+    a.ainv_t = c->ainv_t;
+    a.f_top = f;
+    a.u_top = u;
+    a.done = done;
+    return mgk::launch_tail2d<T>(c->ns[l], a, sep, s, c->slots);
   }
   mgk::TailArgs a{};
   // a tail holding only the coarsest level solves it exactly: a repeated visit with the
@@ -1186,6 +1216,31 @@ mg_status setup_ctx(const mg_config *cfg, void *hip_stream, int slots, bool own_
       hipError_t e = mixed ? mgk::tail_prepare<float>(c->dim, G, c->tail_lds)
                            : mgk::tail_prepare<double>(c->dim, G, c->tail_lds);
       if (e != hipSuccess) return bail(fail(MG_EDEVICE, std::string("tail setup: ") + hipGetErrorString(e)));
+    }
+  }
+  // 2D hierarchies that end in 9^2 take the kernel with compile-time sides, from 65^2 (FP64
+  // separable levels: 33^2) unless MG_TAIL_N sets a smaller top.  Measured against the
+  // general tail from 33^2 and two launches for 65^2: V(2,1) FP64 15.7 us against 25 + 13.
+  if (c->dim == 2 && c->ns[L - 1] == mgk::kTail2dCoarse && cfg->smoother != MG_SMOOTH_RBGS && cfg->restrict_op == 1) {
+    int cap = 65, lds_limit = 0;
+    if (const char *tn = std::getenv("MG_TAIL_N")) cap = std::atoi(tn);
+    if (hipDeviceGetAttribute(&lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device) != hipSuccess)
+      lds_limit = 65536;
+    int top = L - 1;
+    bool sep = false;
+    for (int l = L - 2; l >= 0 && c->ns[l] <= cap && c->ns[l] <= 65; --l) {
+      const bool sep_l = sep || !c->ops[l].cross;
+      const size_t need = mixed ? mgk::tail2d_lds_bytes<float>(c->ns[l], sep_l)
+                                : mgk::tail2d_lds_bytes<double>(c->ns[l], sep_l);
+      if (need > (size_t)lds_limit) break;
+      top = l;
+      sep = sep_l;
+    }
+    if (top < L - 1) {
+      hipError_t e = mixed ? mgk::tail2d_prepare<float>(c->ns[top], sep) : mgk::tail2d_prepare<double>(c->ns[top], sep);
+      if (e != hipSuccess) return bail(fail(MG_EDEVICE, std::string("tail setup: ") + hipGetErrorString(e)));
+      c->tail2d = true;
+      c->tail_top = top;
     }
   }
   if (c->dim == 3) {

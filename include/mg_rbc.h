@@ -37,7 +37,8 @@
  * the inverse formed at set-up), the correction interpolated with (1/4)]. 1 .; 1 4 1; . 1 .[ (C points copy, F
  * points take the mean of their four C neighbours) and added, nu2 sweeps.  The levels of
  * side <= 33 (environment MG_RBC_TAIL: another side, 0 for none) run in one workgroup
- * launch per visit, with the same arithmetic as the per-level kernels.
+ * launch per visit; above them each half of a level's visit is one pass (environment
+ * MG_RBC_PASSES=0: separate launches per step), with the same arithmetic.
  *
  * Status codes and mg_last_error() are those of mg.h.  Every call is asynchronous on the
  * handle's stream unless it returns a host value.  Calls on one handle must not overlap.

@@ -7,10 +7,12 @@
 // is padding and stays zero).  Every
 // level's operator is a symmetric stencil of at most four coefficients on that storage
 // grid: centre, axis neighbours at distance 1, diagonal neighbours, axis neighbours at
-// distance 2.  The omega-Jacobi partial steps and the interpolation are one thread per
-// array entry, reading the few neighbours they need through the caches; the restriction
-// forms the defect once per point in an LDS tile; the coarsest level is solved by its
-// inverse, formed on the host at set-up and applied in one workgroup.
+// distance 2.  A cycle runs each level's half visits as one pass each (rbc_passes.hip) from
+// side 17 up, the small levels in one workgroup.  The separate kernels of this file (the
+// single-step entry points, cycles without a sweep on one side, MG_RBC_PASSES=0) are one
+// thread per array entry for the omega-Jacobi partial steps and the interpolation, an LDS
+// tile for the defect and restriction; the coarsest level is solved by its inverse, formed
+// on the host at set-up and applied in one workgroup.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -22,12 +24,11 @@
 
 #include "batch.h"
 #include "mg_rbc.h"
+#include "rbc_passes.h"
 
 namespace {
 
-struct Op {
-  double c0, a1, d1, a2;  // centre, axis +-1, diagonal, axis +-2
-};
+using Op = mgk::RbcOp;
 
 constexpr int kBX = 64, kBY = 4;          // one wavefront per storage row segment
 constexpr int kMaxCoarseSide = 17;        // storage side of the largest coarsest level
@@ -323,7 +324,8 @@ __device__ __forceinline__ void coarsest_solve(const double *f, double *u, const
 __global__ __launch_bounds__(1024) void k_rbc_coarsest(const double *f, double *u,
                                                        const double *__restrict__ ainv_t,
                                                        const int *__restrict__ pos, int K,
-                                                       int entries) {
+                                                       int entries, const int *done) {
+  if (done != nullptr && *done != 0) return;
   coarsest_solve(f, u, ainv_t, pos, K, entries);
 }
 
@@ -353,6 +355,7 @@ struct TailArgs {
   const double *ainv_t;
   const int *pos;
   int K;
+  const int *done;  // may be null: nothing is done when it is set
 };
 
 // The defect at point (a, b) of a level, zero off its unknowns.
@@ -431,6 +434,7 @@ __device__ void tail_prolong(const TailLevel &L, const TailLevel &C) {
 // smooths and restricts; a finished visit of level l + 1 either starts the next one (the
 // second visit of a W-cycle, bit l of `again`) or lets level l interpolate and smooth.
 __global__ __launch_bounds__(1024) void k_rbc_tail(TailArgs a) {
+  if (a.done != nullptr && *a.done != 0) return;
   const int last = a.nl - 1;
   for (int v = 0; v < a.visits; ++v) {
     int l = 0;
@@ -499,6 +503,51 @@ __global__ __launch_bounds__(256) void k_rbc_sum(const double *__restrict__ part
     __syncthreads();
   }
   if (threadIdx.x == 0) out[0] = sqrt(red[0] * scale);
+}
+
+// The stopping state of a solve on the device; the checks' results go to pinned host memory
+// as they are made (HostState).
+struct SolveState {
+  int done, checks;
+  double r0;
+};
+struct HostState {
+  volatile int checks;  // written last
+  int done;
+  double hist[MG_MAX_HISTORY + 1];
+};
+
+// The residual norm before a cycle from the first pass's partial sums, and the stopping
+// rule: at rtol r0, at max_cycles, or at a norm that is not finite after the first.
+__global__ __launch_bounds__(256) void k_rbc_check(SolveState *st, HostState *host, const double *__restrict__ partial,
+                                                   int count, double scale, double rtol, int max_cycles) {
+  __shared__ double red[256];
+  if (st->done != 0) return;
+  double s = 0.0;
+  for (int q = threadIdx.x; q < count; q += blockDim.x) s += partial[q];
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x != 0) return;
+  const double r = sqrt(red[0] * scale);
+  const int k = st->checks;
+  if (k == 0) st->r0 = r;
+  const bool stop = !(r > rtol * st->r0) || k >= max_cycles || (k > 0 && !isfinite(r));
+  st->checks = k + 1;
+  st->done = stop ? 1 : 0;
+  host->hist[k] = r;
+  host->done = stop ? 1 : 0;
+  __threadfence_system();
+  host->checks = k + 1;
+}
+
+__global__ void k_rbc_start(SolveState *st) {
+  st->done = 0;
+  st->checks = 0;
+  st->r0 = 0.0;
 }
 
 struct Level {
@@ -630,10 +679,14 @@ struct mg_rbc_ctx {
   hipStream_t stream = nullptr;
   std::vector<Level> lv;
   std::vector<double *> u, f, t;  // per level; u[0], f[0] are the caller's
+  std::vector<double *> t2;       // second sweep target (an odd number of passes per visit)
+  SolveState *state = nullptr;
+  HostState *host = nullptr;      // pinned
   double *partial = nullptr, *norm_dev = nullptr, *norm_host = nullptr;
   double *ainv_t = nullptr;  // the coarsest operator's inverse, transposed (K x K)
   int *pos = nullptr;        // array index of each coarsest unknown
   int coarse_k = 0;
+  bool passes = true;        // levels of side >= 17 run as passes (rbc_passes.hip)
   int tail_top = 1 << 30;    // first level of the one-workgroup tail (none: past the last)
 };
 
@@ -704,7 +757,7 @@ mg_status launch_prolong(mg_rbc_ctx *h, int l, const double *ec, const double *u
 
 // Levels tail_top .. last in one launch, the top level's arrays f and u, visited `visits`
 // times in a row.
-mg_status launch_tail(mg_rbc_ctx *h, const double *f, double *u, int visits) {
+mg_status launch_tail(mg_rbc_ctx *h, const double *f, double *u, int visits, const int *done) {
   const int top = h->tail_top, last = (int)h->lv.size() - 1;
   TailArgs a{};
   a.nl = last - top + 1;
@@ -721,14 +774,15 @@ mg_status launch_tail(mg_rbc_ctx *h, const double *f, double *u, int visits) {
   a.ainv_t = h->ainv_t;
   a.pos = h->pos;
   a.K = h->coarse_k;
+  a.done = done;
   hipLaunchKernelGGL(k_rbc_tail, dim3(1), dim3(1024), 0, h->stream, a);
   RBC_HIP(hipGetLastError());
   return MG_OK;
 }
 
-mg_status launch_coarsest(mg_rbc_ctx *h, const double *f, double *u) {
+mg_status launch_coarsest(mg_rbc_ctx *h, const double *f, double *u, const int *done = nullptr) {
   hipLaunchKernelGGL(k_rbc_coarsest, dim3(1), dim3(1024), 0, h->stream, f, u, h->ainv_t, h->pos,
-                     h->coarse_k, (int)level_entries(h->lv.back()));
+                     h->coarse_k, (int)level_entries(h->lv.back()), done);
   RBC_HIP(hipGetLastError());
   return MG_OK;
 }
@@ -744,17 +798,82 @@ mg_status sweep(mg_rbc_ctx *h, int l, const double *f, double *u) {
   return launch_smooth(h, l, 2, f, h->t[l], u);
 }
 
-mg_status cycle(mg_rbc_ctx *h, int l, const double *f, double *u) {
+// Passes of a level's visit: the nu1 sweeps (the last one with the defect and restriction),
+// then max(1, nu2) (the first one with the interpolation).  They write alternately u and t
+// and the last one u; with an odd number the first writes t2.
+int visit_passes(const mg_rbc_config &c) { return c.nu1 + std::max(1, c.nu2); }
+bool needs_t2(const mg_rbc_config &c) { return c.nu1 > 0 && visit_passes(c) % 2 == 1; }
+
+// Whether level l runs as passes (rbc_passes.hip).  The separate kernels remain for sides
+// below 17, for cycles without a sweep on one side (their passes would be the separate
+// kernels anyway) and with MG_RBC_PASSES=0.  Measured (G1 V(1,1)): a 4097^2 cycle 0.63 ms
+// against 1.46, a 257^2 cycle 0.13 ms against 0.19.
+bool pass_level(const mg_rbc_ctx *h, int l) {
+  return h->passes && l < (int)h->lv.size() - 1 && l < h->tail_top && h->lv[l].m >= mgk::kRbcPassSide;
+}
+
+mg_status cycle(mg_rbc_ctx *h, int l, const double *f, double *u, bool zero, bool check, const int *done);
+
+// The coarse visits of level l.
+mg_status visits(mg_rbc_ctx *h, int l, const int *done) {
   const int last = (int)h->lv.size() - 1;
-  if (l == h->tail_top) return launch_tail(h, f, u, 1);
-  if (l == last) return launch_coarsest(h, f, u);
-  for (int k = 0; k < h->cfg.nu1; ++k) RBC_TRY(sweep(h, l, f, u));
-  RBC_TRY(launch_restrict(h, l, f, u, h->f[l + 1], h->u[l + 1]));
   const int reps = l + 1 < last ? h->cfg.gamma : 1;
   if (l + 1 == h->tail_top)  // the visits of the tail's top level in one launch
-    RBC_TRY(launch_tail(h, h->f[l + 1], h->u[l + 1], reps));
-  else
-    for (int k = 0; k < reps; ++k) RBC_TRY(cycle(h, l + 1, h->f[l + 1], h->u[l + 1]));
+    return launch_tail(h, h->f[l + 1], h->u[l + 1], reps, done);
+  for (int k = 0; k < reps; ++k) RBC_TRY(cycle(h, l + 1, h->f[l + 1], h->u[l + 1], k == 0, false, done));
+  return MG_OK;
+}
+
+mg_status cycle_passes(mg_rbc_ctx *h, int l, const double *f, double *u, bool zero, bool check, const int *done) {
+  const Level &L = h->lv[l];
+  const double omega = h->cfg.omega == 0.0 ? 1.0 : h->cfg.omega;
+  const int total = visit_passes(h->cfg);
+  const double *in = zero ? nullptr : u;
+  int k = 0;
+  auto target = [&]() -> double * {
+    double *o = (total - 1 - k) % 2 == 0 ? u : h->t[l];
+    return o == in ? h->t2[l] : o;
+  };
+  // the next level's iterate has to be zeros only where its first step reads it
+  double *uc = pass_level(h, l + 1) ? nullptr : h->u[l + 1];
+  for (; k < h->cfg.nu1; ++k) {
+    const bool last = k == h->cfg.nu1 - 1;
+    double *o = target();
+    int np = 0;
+    RBC_HIP(mgk::launch_rbc_pre(L.odd, L.op, omega, f, in, o, last ? h->f[l + 1] : nullptr, last ? uc : nullptr,
+                                L.m, check && k == 0 ? h->partial : nullptr, &np, done, h->stream));
+    in = o;
+    if (check && k == 0) {
+      const double ni = (double)(L.m - 2) * (double)(L.m - 2);
+      hipLaunchKernelGGL(k_rbc_check, dim3(1), dim3(256), 0, h->stream, h->state, h->host, h->partial, np,
+                         1.0 / ni, h->cfg.rtol, h->cfg.max_cycles);
+      RBC_HIP(hipGetLastError());
+    }
+  }
+  RBC_TRY(visits(h, l, done));
+  for (int j = 0; j < h->cfg.nu2; ++j, ++k) {
+    double *o = target();
+    if (j == 0)
+      RBC_HIP(mgk::launch_rbc_post(L.odd, L.op, omega, h->u[l + 1], in, f, o, L.m, done, h->stream));
+    else
+      RBC_HIP(mgk::launch_rbc_pre(L.odd, L.op, omega, f, in, o, nullptr, nullptr, L.m, nullptr, nullptr, done,
+                                  h->stream));
+    in = o;
+  }
+  return in == u ? MG_OK : fail(MG_EDEVICE, "sweep targets out of order");
+}
+
+// One cycle from level l (zero: from the zero iterate, which u then holds unless the level
+// runs as passes).  check, done: a solve's first pass forms the residual norm, and every
+// launch returns at once when *done is set (passes on every level above the tail only).
+mg_status cycle(mg_rbc_ctx *h, int l, const double *f, double *u, bool zero, bool check, const int *done) {
+  const int last = (int)h->lv.size() - 1;
+  if (l == h->tail_top) return launch_tail(h, f, u, 1, done);
+  if (l == last) return launch_coarsest(h, f, u, done);
+  if (pass_level(h, l)) return cycle_passes(h, l, f, u, zero, check, done);
+  for (int k = 0; k < h->cfg.nu1; ++k) RBC_TRY(sweep(h, l, f, u));
+  RBC_TRY(launch_restrict(h, l, f, u, h->f[l + 1], h->u[l + 1]));
+  RBC_TRY(visits(h, l, done));
   RBC_TRY(launch_prolong(h, l, h->u[l + 1], u, u));
   for (int k = 0; k < h->cfg.nu2; ++k) RBC_TRY(sweep(h, l, f, u));
   return MG_OK;
@@ -772,6 +891,55 @@ mg_status norm(mg_rbc_ctx *h, const double *f, const double *u, double *out) {
   RBC_HIP(hipMemcpyAsync(h->norm_host, h->norm_dev, sizeof(double), hipMemcpyDeviceToHost, h->stream));
   RBC_HIP(hipStreamSynchronize(h->stream));
   *out = *h->norm_host;
+  return MG_OK;
+}
+
+// Whether every launch of a cycle takes the stopping flag (so that a solve can run ahead of
+// its checks): passes on every level above the tail or the coarsest level.
+bool solve_on_device(const mg_rbc_ctx *h) {
+  const int below = std::min((int)h->lv.size() - 1, h->tail_top);
+  if (below == 0) return false;
+  for (int l = 0; l < below; ++l)
+    if (!pass_level(h, l)) return false;
+  return true;
+}
+
+// Waits until the host has the result of `checks` checks; an error if the stream ends or
+// fails first.
+mg_status wait_checks(mg_rbc_ctx *h, int checks) {
+  for (unsigned spin = 0; h->host->checks < checks; ++spin) {
+    if (spin % 1024 != 1023) continue;
+    const hipError_t e = hipStreamQuery(h->stream);
+    if (e == hipErrorNotReady) continue;
+    RBC_HIP(e);
+    if (h->host->checks < checks) return fail(MG_EDEVICE, "the stopping check did not report");
+  }
+  __atomic_thread_fence(__ATOMIC_ACQUIRE);
+  return MG_OK;
+}
+
+// mg_rbc_solve with the stopping rule on the device: cycle k + 1 is enqueued when check k
+// (made by the first pass of cycle k) has come back, while the rest of cycle k runs, so the
+// device does not wait for the host; the launches after the check that stops return at
+// once and leave u as it is.  4097^2 G1 V(1,1): the separate norm pass took 82 us and the
+// round trip to the host about 20 us of each 1.56 ms cycle.
+mg_status solve_async(mg_rbc_ctx *h, const double *f, double *u, int *cycles, double *hist) {
+  h->host->checks = 0;
+  h->host->done = 0;
+  hipLaunchKernelGGL(k_rbc_start, dim3(1), dim3(1), 0, h->stream, h->state);
+  RBC_HIP(hipGetLastError());
+  int k = 0;
+  for (;; ++k) {
+    RBC_TRY(cycle(h, 0, f, u, false, true, &h->state->done));
+    RBC_TRY(wait_checks(h, k + 1));
+    if (h->host->done) break;
+  }
+  RBC_HIP(hipStreamSynchronize(h->stream));
+  if (cycles) *cycles = k;
+  if (hist) std::memcpy(hist, h->host->hist, (size_t)(k + 1) * sizeof(double));
+  const double r0 = h->host->hist[0], r = h->host->hist[k];
+  if (k > 0 && !std::isfinite(r)) return fail(MG_ENUMERIC, "residual norm is not finite");
+  if (r > h->cfg.rtol * r0) return fail(MG_ENOCONV, "solve did not reach rtol");
   return MG_OK;
 }
 
@@ -809,12 +977,20 @@ mg_status mg_rbc_setup(const mg_rbc_config *cfg, void *stream, mg_rbc_ctx **out)
   h->u.assign(cfg->levels, nullptr);
   h->f.assign(cfg->levels, nullptr);
   h->t.assign(cfg->levels, nullptr);
+  h->t2.assign(cfg->levels, nullptr);
+  {
+    const char *e = getenv("MG_RBC_PASSES");
+    h->passes = !(e != nullptr && *e != 0 && atoi(e) == 0) && cfg->nu1 > 0 && cfg->nu2 > 0;
+  }
   for (int l = 0; l < cfg->levels && ok; ++l) {
     const size_t cnt = level_entries(h->lv[l]);
+    if (h->passes && needs_t2(*cfg) && h->lv[l].m >= mgk::kRbcPassSide) ok = ok && alloc(&h->t2[l], cnt);
     if (l > 0) ok = ok && alloc(&h->u[l], cnt) && alloc(&h->f[l], cnt);
     ok = ok && alloc(&h->t[l], cnt);
   }
-  ok = ok && alloc(&h->partial, kNormBlocks) && alloc(&h->norm_dev, 1);
+  ok = ok && alloc(&h->partial, std::max(kNormBlocks, mgk::rbc_pre_partials(cfg->n))) && alloc(&h->norm_dev, 1);
+  ok = ok && hipMalloc((void **)&h->state, sizeof(SolveState)) == hipSuccess &&
+       hipHostMalloc((void **)&h->host, sizeof(HostState), hipHostMallocDefault) == hipSuccess;
   std::vector<double> inv_t;
   std::vector<int> pos;
   if (ok && !coarsest_inverse(h->lv.back(), inv_t, pos)) {
@@ -852,6 +1028,7 @@ mg_status mg_rbc_setup(const mg_rbc_config *cfg, void *stream, mg_rbc_ctx **out)
     hipError_t e = hipMemsetAsync(h->u[l], 0, bytes, h->stream);
     if (e == hipSuccess) e = hipMemsetAsync(h->f[l], 0, bytes, h->stream);
     if (e == hipSuccess) e = hipMemsetAsync(h->t[l], 0, bytes, h->stream);
+    if (e == hipSuccess && h->t2[l]) e = hipMemsetAsync(h->t2[l], 0, bytes, h->stream);
     if (e != hipSuccess) {
       mg_rbc_destroy(h);
       return fail(MG_EDEVICE, std::string("hipMemsetAsync: ") + hipGetErrorString(e));
@@ -871,6 +1048,9 @@ void mg_rbc_destroy(mg_rbc_ctx *h) {
   for (double *p : h->u) release(p);
   for (double *p : h->f) release(p);
   for (double *p : h->t) release(p);
+  for (double *p : h->t2) release(p);
+  if (h->state) (void)hipFree(h->state);
+  if (h->host) (void)hipHostFree(h->host);
   release(h->partial);
   release(h->norm_dev);
   release(h->ainv_t);
@@ -891,7 +1071,7 @@ int mg_rbc_level_pitch(const mg_rbc_ctx *h, int level) {
 
 mg_status mg_rbc_cycles(mg_rbc_ctx *h, const double *f, double *u, int ncycles) {
   if (!h || !f || !u || ncycles < 0) return fail(MG_EINVAL, "bad argument");
-  for (int k = 0; k < ncycles; ++k) RBC_TRY(cycle(h, 0, f, u));
+  for (int k = 0; k < ncycles; ++k) RBC_TRY(cycle(h, 0, f, u, false, false, nullptr));
   return MG_OK;
 }
 
@@ -902,6 +1082,7 @@ mg_status mg_rbc_residual_norm(mg_rbc_ctx *h, const double *f, const double *u, 
 
 mg_status mg_rbc_solve(mg_rbc_ctx *h, const double *f, double *u, int *cycles, double *hist) {
   if (!h || !f || !u) return fail(MG_EINVAL, "bad argument");
+  if (solve_on_device(h)) return solve_async(h, f, u, cycles, hist);
   double r0 = 0.0, r = 0.0;
   RBC_TRY(norm(h, f, u, &r0));
   if (hist) hist[0] = r0;
@@ -909,7 +1090,7 @@ mg_status mg_rbc_solve(mg_rbc_ctx *h, const double *f, double *u, int *cycles, d
   r = r0;
   mg_status st = MG_OK;
   while (r > h->cfg.rtol * r0 && k < h->cfg.max_cycles) {
-    RBC_TRY(cycle(h, 0, f, u));
+    RBC_TRY(cycle(h, 0, f, u, false, false, nullptr));
     RBC_TRY(norm(h, f, u, &r));
     ++k;
     if (hist) hist[k] = r;

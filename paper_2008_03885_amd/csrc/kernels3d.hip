@@ -1169,20 +1169,45 @@ KOp<T> to_kop3(const LevelOp &op, double omega) {
   return k;
 }
 
-// Plane bands of the 3D kernels: 8..64 fine planes (4..32 coarse), about four rounds of
-// resident blocks per launch (the plane loop of a block is latency-bound, so several
-// blocks per CU in flight beat one long march each).
+// Plane bands of the 3D kernels: 8..64 fine planes (4..32 coarse).  The defect + full
+// weighting takes about four rounds of resident blocks per launch; the cross sweep and the
+// interpolation one round where a level has that few tiles (every band loads a ring of
+// planes before its first output: 257^3 FP64 sweep in bands of 64 planes 86 us, of 24 98 us,
+// interpolation in bands of 128 planes 62 us, of 40 89 us).
 constexpr int kMinPlanes = 8, kMaxPlanes = 64, kRounds3d = 4;
+
+// Planes per band of the pencil sweep.  A band of zc planes marches zc + 6 (six fill its
+// rings) in turns of eight, so zc = 8 j + 2; a launch takes about as many turns as rounds of
+// resident blocks times turns per band.  The band with the fewest, and of those the one
+// with the least work in all.  Measured against bands of 8 to 64 planes (whole turns of
+// planes, four rounds; one sweep, us): FP64 33^3 12.6 -> 7.2, 65^3 13.5 -> 12.8, 129^3
+// 37.6 -> 26.7, 257^3 156 -> 130, 513^3 1009 -> 909; FP32 11.2 -> 6.5, 11.8 -> 10.5,
+// 24.6 -> 19.0, 86.5 -> 67.2, 538 -> 485.
+int gpen_planes(int n, int tiles, int capacity, int zmin) {
+  int best = 0;
+  long rounds0 = 0, work0 = 0;
+  for (int zc = zmin <= 2 ? 2 : (zmin + 5) / 8 * 8 + 2; zc <= 130; zc += 8) {
+    const long blocks = (long)tiles * ((n + zc - 1) / zc);
+    const long rounds = (blocks + capacity - 1) / capacity * (zc + 6), work = blocks * (zc + 6);
+    if (best == 0 || rounds < rounds0 || (rounds == rounds0 && work < work0)) {
+      best = zc;
+      rounds0 = rounds;
+      work0 = work;
+    }
+  }
+  return best;
+}
 
 // Whether a level takes the wide tiles (64 fine columns) in the cross kernels: rows of
 // 256 bytes and more keep the HBM pages of a plane busy on the large levels, while the
-// narrow tiles give more blocks on the small ones.  Environment variable `var` = 0 or 1
-// forces the choice.
+// narrow tiles give more blocks on the small ones.  From 64 MB an array, which takes in
+// 257^3 FP32 (sweep 51 -> 46 us; 129^3 FP64 is 17 MB).  Environment variable `var` = 0 or
+// 1 forces the choice.
 template <typename T>
 bool wide_tiles(int n, const char *var) {
   const char *e = getenv(var);
   if (e != nullptr && *e != 0) return atoi(e) != 0;
-  return (size_t)n * n * n * sizeof(T) >= ((size_t)96 << 20);
+  return (size_t)n * n * n * sizeof(T) >= ((size_t)64 << 20);
 }
 
 template <typename T, typename TO, int XW, int RR = 2, int YS = 1>
@@ -1297,7 +1322,8 @@ hipError_t launch_sweep_3d(int mode, const LevelOp &op, double omega, const T *f
     const int yr = Y1 * gpen_rows_scale<T>(n);
     const void *fn = yr == Y1 ? gpen3d_fn_rows<T, TO, Y1>(mode) : gpen3d_fn_rows<T, TO, Y2>(mode);
     const int ptiles = cdiv(n, 58) * cdiv(n, 4 * yr);
-    const int pzc = (std::min(kMaxPlanes, band_rows(n, ptiles, kRounds3d * resident_blocks(fn, 256, 0), kMinPlanes)) + 7) / 8 * 8;
+    // partial sums are sized for bands of at least kMinPlanes planes
+    const int pzc = gpen_planes(n, ptiles, resident_blocks(fn, 256, 0), partials != nullptr ? kMinPlanes : 2);
     const dim3 pgrid(cdiv(n, 58), cdiv(n, 4 * yr), cdiv(n, pzc));
     if (nparts) *nparts = pgrid.x * pgrid.y * pgrid.z;
 #define MG_GP(MODE, YR) hipLaunchKernelGGL((k_gpen3d<T, TO, MODE, YR>), pgrid, dim3(256), 0, s, f, u, out, n, pzc, k, partials, done)
@@ -1326,8 +1352,8 @@ hipError_t launch_sweep_3d(int mode, const LevelOp &op, double omega, const T *f
   const int tiles = cdiv(n - 1, xw) * cdiv(n - 1, TY * ys);
   const void *occ_fn = x3path ? xsweep3d_fn<T, TO, 64, 3>(mode, true) : sweep3d_fn<T, TO>(mode, u != nullptr, xw, ys);
   const int zr = x3path ? 16 : kZR;  // planes per loop turn of the kernel
-  const int zc = (std::min(kMaxPlanes, band_rows(n, tiles, kRounds3d * resident_blocks(occ_fn, nt, 0),
-                                                 kMinPlanes)) + zr - 1) / zr * zr;
+  const int zc = (std::min(kMaxPlanes, band_rows(n - 1, tiles, resident_blocks(occ_fn, nt, 0), kMinPlanes)) + zr - 1) /
+                 zr * zr;
   const dim3 grid(cdiv(n - 1, xw), cdiv(n - 1, TY * ys), cdiv(n - 1, zc));
   if (nparts) *nparts = grid.x * grid.y * grid.z;
   if (x3path) {
@@ -1443,8 +1469,8 @@ hipError_t launch_sweep_corr_3d(const LevelOp &op, double omega, const float *f,
                  : xw == 64  ? (const void *)k_xsweep3d<float, double, kSweepCorr, true, 64, 2, 2>
                              : (const void *)k_xsweep3d<float, double, kSweepCorr, true, TX, 2, 1>;
   const int tiles = cdiv(n - 1, xw) * cdiv(n - 1, TY * ys);
-  const int zc = (std::min(kMaxPlanes, band_rows(n, tiles, kRounds3d * resident_blocks(fn, nt, 0), kMinPlanes)) +
-                  kZR - 1) / kZR * kZR;
+  const int zc = (std::min(kMaxPlanes, band_rows(n - 1, tiles, resident_blocks(fn, nt, 0), kMinPlanes)) + kZR - 1) /
+                 kZR * kZR;
   const dim3 grid(cdiv(n - 1, xw), cdiv(n - 1, TY * ys), cdiv(n - 1, zc));
   const KOp<float> k = to_kop3<float>(op, omega);
   if (xw == 128)
@@ -1525,9 +1551,13 @@ hipError_t launch_prolong_correct_3d(int prolong, const T *v, const T *uin, T *u
   const int tiles = cdiv(n - 1, xw) * cdiv(n - 1, TY);
   const void *fn = xw == 64 ? (prolong == 3 ? (const void *)k_prolong3d<T, 3, 64> : (const void *)k_prolong3d<T, 1, 64>)
                             : (prolong == 3 ? (const void *)k_prolong3d<T, 3, TX> : (const void *)k_prolong3d<T, 1, TX>);
-  // bands of whole turns (8 planes): no block stores outside its planes; the last band
-  // takes the remainder (for n = 2^k + 1 the boundary plane)
-  const int zc = (std::min(kMaxPlanes, band_rows(n, tiles, kRounds3d * resident_blocks(fn, nt, 0), kMinPlanes)) + 7) / 8 * 8;
+  // bands of a power of two of planes, at least 8 (whole turns): no block stores outside its
+  // planes; the last band takes the remainder (for n = 2^k + 1 the boundary plane).  One
+  // round of resident blocks, at most 128 planes in FP64 and 64 in FP32 (1025^3: FP64 64
+  // planes 4254, 128 3974 us; FP32 2204 and 2366 us)
+  const int want = std::min(band_rows(n - 1, tiles, resident_blocks(fn, nt, 0), kMinPlanes), sizeof(T) == 8 ? 128 : 64);
+  int zc = 8;
+  while (zc < want) zc *= 2;
   const dim3 grid(cdiv(n - 1, xw), cdiv(n - 1, TY), std::max(1, (n - 1) / zc));
 #define MG_P3(PP, XW) hipLaunchKernelGGL((k_prolong3d<T, PP, XW>), grid, dim3(nt), 0, s, v, uin, uout, n, zc, done)
   if (xw == 64) {

@@ -408,17 +408,18 @@ size_t entries_bytes(const mg_config *cfg, int L) {
 // also interpolates and corrects).  Passes alternate between u and t and must end in u;
 // with an odd number of passes the first one writes a third array t2.
 int rb_passes(const mg_config *cfg) { return std::max(1, cfg->nu1) + std::max(1, cfg->nu2); }
-// 3D red-black sweeps of FP64 cross levels in one pass (k_rbxsweep3d); MG_RB3_FUSED=0
-// runs the two partial steps as separate launches.  Measured at 513^3: FP64 solves 56.4
-// against 60.9 ms; FP32 cycles are faster as two launches (mixed 44.0 against 39.8 ms).
-bool rb3_fused() {
-  static const bool on = [] {
+// 3D red-black sweeps of FP64 cross levels in one pass (k_rbxsweep3d) from 1025^3: the pass
+// reads u and f once for two steps but marches latency-bound on a 60 x 8 tile.  Measured
+// per V(2,1) cycle, one pass against two launches (ms): 65^3 0.317 / 0.168, 257^3 1.24 /
+// 1.09, 513^3 6.84 / 6.40, 1025^3 49.4 / 52.7.  MG_RB3_FUSED = 0 or 1 forces it off or on.
+constexpr int kOnePassSide3d = 1025;
+bool rb3_fused(int n) {
+  static const int on = [] {
     const char *e = std::getenv("MG_RB3_FUSED");
-    return e == nullptr || std::atoi(e) != 0;
+    return e == nullptr || *e == 0 ? -1 : std::atoi(e) != 0 ? 1 : 0;
   }();
-  return on;
+  return on < 0 ? n >= kOnePassSide3d : on != 0;
 }
-
 bool needs_t2(const mg_config *cfg) {
   return cfg->dim == 2 && cfg->smoother == MG_SMOOTH_RBJ && rb_passes(cfg) % 2 == 1;
 }
@@ -581,13 +582,15 @@ hipError_t resid_restrict(mg_ctx *c, int l, const T *f, const T *u, T *scratch, 
   return mgk::launch_restrict_cubic<T>(c->dim, scratch, fc, c->ns[l], done, s, c->slots);
 }
 
-// Two omega-Jacobi sweeps of a 3D cross level in one pass: FP64 by default; MG_X2=0 or 1
-// sets both precisions.
+// Two omega-Jacobi sweeps of a 3D cross level of side n in one pass: FP64 from 1025^3 (per
+// V(2,1) cycle, one pass against two sweeps, ms: 65^3 0.137 / 0.107, 129^3 0.203 / 0.185,
+// 257^3 0.677 / 0.672, 513^3 4.02 / 3.83, 1025^3 30.3 / 30.9); MG_X2=0 or 1 sets every side
+// and both precisions.
 template <typename T>
-bool x2_enabled() {
+bool x2_enabled(int n) {
   const char *e = std::getenv("MG_X2");
   if (e != nullptr && *e != 0) return std::atoi(e) != 0;
-  return sizeof(T) == 8;
+  return sizeof(T) == 8 && n >= kOnePassSide3d;
 }
 
 // Two omega-Jacobi sweeps from a zero iterate in one 3D pass unless MG_Z2=0.
@@ -686,7 +689,7 @@ bool fuse_corr(const mg_ctx *c) {
   const LevelOp &op = c->ops[0];
   return on && c->cfg.precision == MG_PREC_MIXED && c->dim == 3 && c->L > 1 && c->tail_top > 0 &&
          op.cross && !op.cross3 && c->cfg.smoother == MG_SMOOTH_JACOBI && c->cfg.nu2 >= 1 &&
-         !x2_enabled<float>() && c->slots == 1;
+         !x2_enabled<float>(c->ns[0]) && c->slots == 1;
 }
 
 template <typename T>
@@ -768,7 +771,7 @@ hipError_t cycle(mg_ctx *c, std::vector<Buffers> &B, int l, T *u, const T *f, bo
   // a red-black sweep is two steps: the red points (colour 1), then the black ones (2);
   // on 3D cross levels one launch does both
   const bool rb = c->cfg.smoother == MG_SMOOTH_RBJ || c->cfg.smoother == MG_SMOOTH_RBGS;
-  const bool rb3 = c->cfg.smoother == MG_SMOOTH_RBJ && dim == 3 && op.cross && sizeof(T) == 8 && rb3_fused();
+  const bool rb3 = c->cfg.smoother == MG_SMOOTH_RBJ && dim == 3 && op.cross && sizeof(T) == 8 && rb3_fused(n);
   const int steps = rb && !rb3 ? 2 : 1;
   // Gauss-Seidel steps do not form the defect norm: the stopping check gets its own pass
   const bool gs_check = check && c->cfg.smoother == MG_SMOOTH_RBGS && gs_level(op) && c->cfg.nu1 > 0;
@@ -798,7 +801,7 @@ hipError_t cycle(mg_ctx *c, std::vector<Buffers> &B, int l, T *u, const T *f, bo
   }
   // two omega-Jacobi sweeps of a 3D cross level in one pass where two remain (FP64: 1025^3
   // 10.8 ms against two sweeps of 6.27; in FP32 the pass takes 7.74 ms against 2 x 3.58)
-  const bool x2 = !rb && !rb3 && dim == 3 && op.cross && x2_enabled<T>();
+  const bool x2 = !rb && !rb3 && dim == 3 && op.cross && x2_enabled<T>(n);
   for (int k = k0; k < c->cfg.nu1 * steps; ++k) {
     const bool first_check = check && k == 0 && !gs_check;
     int np = 0;

@@ -379,7 +379,7 @@ __global__ __launch_bounds__(kBlock) void k_coarsest(const double *__restrict__ 
 // record = 0: store sum f^2 (the partials of a zero-u residual pass).  record = 1:
 // relative residual of the latest pass into the history and the stopping decision.
 __global__ __launch_bounds__(kBlock) void k_check(DevState *st, const double *__restrict__ partials,
-                                                  int np, int record) {
+                                                  int np, int record, DevState *mirror) {
   st += blockIdx.z;
   partials += (size_t)blockIdx.z * np;
   if (record && st->done) return;
@@ -416,6 +416,14 @@ __global__ __launch_bounds__(kBlock) void k_check(DevState *st, const double *__
   if (status != 0) {
     st->status = status;
     st->done = 1;
+  }
+  if (mirror != nullptr) {
+    if (c < kMaxHistory) mirror->hist[c] = rel;
+    mirror->last_ratio = st->last_ratio;
+    mirror->status = status;
+    mirror->done = status != 0 ? 1 : 0;
+    __threadfence_system();
+    *(volatile int *)&mirror->checks = c + 1;
   }
 }
 
@@ -619,8 +627,9 @@ hipError_t launch_coarsest(int dim, const double *ainv_t, const T *g, T *v, int 
 }
 
 hipError_t launch_check(DevState *st, const double *partials, int nparts, int record,
-                        hipStream_t s, int slots) {
-  hipLaunchKernelGGL(k_check, dim3(1, 1, slots), dim3(kBlock), 0, s, st, partials, nparts, record);
+                        hipStream_t s, int slots, DevState *mirror) {
+  if (mirror != nullptr && slots != 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_check, dim3(1, 1, slots), dim3(kBlock), 0, s, st, partials, nparts, record, mirror);
   return hipGetLastError();
 }
 

@@ -146,9 +146,10 @@ template <typename T>
 hipError_t launch_coarsest(int dim, const double *ainv_t, const T *g, T *v, int nc,
                            const int *done, hipStream_t s, int slots = 1);
 
-// nparts: partial sums per slot (slot k reads partials[k * nparts ...]).
+// nparts: partial sums per slot (slot k reads partials[k * nparts ...]).  mirror (record = 1,
+// one slot; may be null): pinned host memory that gets the result fields, `checks` last.
 hipError_t launch_check(DevState *st, const double *partials, int nparts, int record,
-                        hipStream_t s, int slots = 1);
+                        hipStream_t s, int slots = 1, DevState *mirror = nullptr);
 
 hipError_t launch_ir_correct(int dim, double *u, const float *e, int n, const int *done,
                              hipStream_t s, int slots = 1);

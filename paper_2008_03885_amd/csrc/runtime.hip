@@ -7,13 +7,13 @@
 //   Galerkin: a_{l+1} = R a_l P and b_{l+1} = R b_l P in 1D, which is exactly R L_l P for the
 //   tensor-product transfers (eqs. L_H_G, L_H_4G).
 // A solve step is one gamma-cycle (FP64) or one refinement step (MIXED); it is captured
-// once into a HIP graph and replayed.  The residual check runs on the device and sets a
-// flag that makes every later kernel of the step return at once, so the host can launch
-// replays in chunks and read the flag one chunk behind without stalling the GPU.
+// once into a HIP graph and replayed (short steps are launched directly).  The residual
+// check runs on the device and sets a flag that makes every later kernel of the step return
+// at once; it also reports to pinned host memory, and the host launches the next step while
+// the rest of this one runs.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <chrono>
 #include <cmath>
 #include <cstddef>
 #include <cstdio>
@@ -350,8 +350,7 @@ struct mg_ctx {
   double *partials = nullptr;
   int np_max = 0;
   DevState *st = nullptr;
-  int *poll = nullptr;  // pinned host: 2 x {done, checks}
-  hipEvent_t ev[2] = {nullptr, nullptr};
+  DevState *mirror = nullptr;  // pinned host: the state as the checks leave it (checks last)
   hipEvent_t ev_async = nullptr;
   bool async_pending = false;
   hipGraph_t graph = nullptr;
@@ -367,7 +366,6 @@ struct mg_ctx {
   int *eoff = nullptr;     // stencil entry lists of every level (tail kernel)
   double *ecoef = nullptr;
   std::vector<int> ent_begin, ent_count;
-  int chunk = 0;          // steps per replay chunk; 0: chosen from the measured step time
   int slots = 1;         // independent problems of this size (batched launches, grid.z)
   bool own_top = false;  // level-0 FP64 f and u are the handle's (batches), not the caller's
   std::vector<void *> allocs;
@@ -650,7 +648,7 @@ hipError_t cycle_rb2d(mg_ctx *c, std::vector<Buffers> &B, int l, T *u, const T *
                              check && k == 0 ? c->partials : nullptr, &np, done, s, c->slots, true);
     if (e != hipSuccess) return e;
     if (check && k == 0) {
-      e = mgk::launch_check(c->st, c->partials, np, 1, s, c->slots);
+      e = mgk::launch_check(c->st, c->partials, np, 1, s, c->slots, c->mirror);
       if (e != hipSuccess) return e;
     }
     in = o;
@@ -706,7 +704,7 @@ hipError_t cycle(mg_ctx *c, std::vector<Buffers> &B, int l, T *u, const T *f, bo
       e = mgk::launch_sweep<T, T>(dim, mgk::kNormOnly, op, c->omega, f, zero_u ? nullptr : u,
                                   (T *)nullptr, n, c->partials, &np, done, s, c->slots);
       if (e != hipSuccess) return e;
-      e = mgk::launch_check(c->st, c->partials, np, 1, s, c->slots);
+      e = mgk::launch_check(c->st, c->partials, np, 1, s, c->slots, c->mirror);
       if (e != hipSuccess) return e;
     }
     return launch_tail_at<T>(c, l, u, f, zero_u, done, s);
@@ -723,7 +721,7 @@ hipError_t cycle(mg_ctx *c, std::vector<Buffers> &B, int l, T *u, const T *f, bo
                              check ? c->partials : nullptr, &np, done, s, c->slots);
     if (e != hipSuccess) return e;
     if (check) {
-      e = mgk::launch_check(c->st, c->partials, np, 1, s, c->slots);
+      e = mgk::launch_check(c->st, c->partials, np, 1, s, c->slots, c->mirror);
       if (e != hipSuccess) return e;
     }
     if (l + 1 >= c->tail_top) {
@@ -747,7 +745,7 @@ hipError_t cycle(mg_ctx *c, std::vector<Buffers> &B, int l, T *u, const T *f, bo
       e = mgk::launch_sweep<T, T>(dim, mgk::kNormOnly, op, c->omega, f, zero_u ? nullptr : u,
                                   (T *)nullptr, n, c->partials, &np, done, s, c->slots);
       if (e != hipSuccess) return e;
-      e = mgk::launch_check(c->st, c->partials, np, 1, s, c->slots);
+      e = mgk::launch_check(c->st, c->partials, np, 1, s, c->slots, c->mirror);
       if (e != hipSuccess) return e;
     }
     return mgk::launch_coarsest<T>(dim, c->ainv_t, f, u, n, done, s, c->slots);
@@ -760,7 +758,7 @@ hipError_t cycle(mg_ctx *c, std::vector<Buffers> &B, int l, T *u, const T *f, bo
     e = mgk::launch_sweep<T, T>(dim, mgk::kNormOnly, op, c->omega, f, zero ? nullptr : u,
                                 (T *)nullptr, n, c->partials, &np, done, s, c->slots);
     if (e != hipSuccess) return e;
-    e = mgk::launch_check(c->st, c->partials, np, 1, s, c->slots);
+    e = mgk::launch_check(c->st, c->partials, np, 1, s, c->slots, c->mirror);
     if (e != hipSuccess) return e;
   }
   if (zero && c->cfg.nu1 == 0) {
@@ -780,7 +778,7 @@ hipError_t cycle(mg_ctx *c, std::vector<Buffers> &B, int l, T *u, const T *f, bo
     e = mgk::launch_sweep<T, T>(dim, mgk::kNormOnly, op, c->omega, f, zero ? nullptr : u, (T *)nullptr, n,
                                 c->partials, &np, done, s, c->slots);
     if (e != hipSuccess) return e;
-    e = mgk::launch_check(c->st, c->partials, np, 1, s, c->slots);
+    e = mgk::launch_check(c->st, c->partials, np, 1, s, c->slots, c->mirror);
     if (e != hipSuccess) return e;
   }
   if (zero && c->cfg.smoother == MG_SMOOTH_RBGS && gs_level(op) && c->cfg.nu1 > 0) {
@@ -820,7 +818,7 @@ hipError_t cycle(mg_ctx *c, std::vector<Buffers> &B, int l, T *u, const T *f, bo
                                   first_check ? c->partials : nullptr, &np, done, s, c->slots, 0);
     if (e != hipSuccess) return e;
     if (first_check) {
-      e = mgk::launch_check(c->st, c->partials, np, 1, s, c->slots);
+      e = mgk::launch_check(c->st, c->partials, np, 1, s, c->slots, c->mirror);
       if (e != hipSuccess) return e;
     }
     zero = false;
@@ -883,7 +881,7 @@ hipError_t record_step(mg_ctx *c, const double *f, double *u, hipStream_t s) {
   hipError_t e = mgk::launch_sweep<double, float>(c->dim, mgk::kResidual, c->ops[0], c->omega, f, u,
                                                   r32, c->ns[0], c->partials, &np, done, s, c->slots);
   if (e != hipSuccess) return e;
-  e = mgk::launch_check(c->st, c->partials, np, 1, s, c->slots);
+  e = mgk::launch_check(c->st, c->partials, np, 1, s, c->slots, c->mirror);
   if (e != hipSuccess) return e;
   const bool fuse = fuse_corr(c);
   for (int i = 0; i < c->cfg.inner_cycles; ++i) {
@@ -938,6 +936,7 @@ mg_status begin_solve(mg_ctx *c, const double *f, double *u, double rtol, int ma
   MG_HIP(hipSetDevice(c->device));
   mg_status st = ensure_graph(c, f, u);
   if (st != MG_OK) return st;
+  std::memset(c->mirror, 0, sizeof(DevState));  // no work of an earlier solve is left
   hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, c->stream, c->st, rtol, max_steps + 1,
                      floor_detect);
   MG_HIP(hipGetLastError());
@@ -977,65 +976,43 @@ void result_from_state(const mg_ctx *c, const DevState &hs, mg_result *res, mg_s
   }
 }
 
+// The finished solve's result: the stream has passed every step.
 mg_status fill_result(mg_ctx *c, mg_result *res, mg_status *outcome) {
-  DevState hs;
-  MG_HIP(hipMemcpyAsync(&hs, c->st, sizeof(DevState), hipMemcpyDeviceToHost, c->stream));
   MG_HIP(hipStreamSynchronize(c->stream));
-  result_from_state(c, hs, res, outcome);
+  result_from_state(c, *c->mirror, res, outcome);
   return MG_OK;
 }
 
-// Replay policy.  Steps are replayed in chunks, and the host reads the stopping flag of
-// chunk k-1 while chunk k runs, so the device never waits for the host.  Every step
-// replayed after convergence still launches its kernels, which return at once (a few
-// microseconds each: a W-cycle on eight levels is some two thousand launches).  So the
-// chunk is sized from the measured step time to about kChunkSeconds, and steps longer
-// than kSyncStepSeconds are run one at a time with no lookahead: the host turnaround
-// (tens of microseconds) then costs less than one replay past convergence.
-constexpr double kChunkSeconds = 3e-4, kSyncStepSeconds = 2e-3;
-
-double wall_seconds() {
-  return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
+// Waits until `checks` checks have reached the mirror; an error if the stream ends or fails
+// first.
+mg_status wait_checks(mg_ctx *c, int checks) {
+  const volatile int *seen = &c->mirror->checks;
+  for (unsigned spin = 1; *seen < checks; ++spin) {
+    if (spin % 1024 != 0) continue;
+    const hipError_t e = hipStreamQuery(c->stream);
+    if (e == hipErrorNotReady) continue;
+    MG_HIP(e);
+    if (*seen < checks) return fail(MG_EDEVICE, "a residual check did not report");
+  }
+  __atomic_thread_fence(__ATOMIC_ACQUIRE);
+  return MG_OK;
 }
 
+// A step makes its residual check at its start, and the check also writes the state to
+// pinned host memory.  So step k + 1 is launched as soon as check k is seen, while the rest
+// of step k runs: the device does not wait for the host, and at most the rest of one step
+// runs (returning at once) past the stopping test.  Against copying the flag back once per
+// chunk of steps: 513^2 mixed 1.31 -> 1.18 ms, 65^3 FP64 2.49 -> 2.33 ms, 65^2
+// FP64 739 -> 563 us.
 mg_status run(mg_ctx *c, const double *f, double *u, double rtol, int max_steps, int floor_detect,
               mg_result *res) {
   mg_status st = begin_solve(c, f, u, rtol, max_steps, floor_detect);
   if (st != MG_OK) return st;
-  const int total = max_steps + 1;
-  int launched = 0, k = 0, chunk = c->chunk > 0 ? c->chunk : 1, prev_cnt = 0;
-  bool lookahead = true;
-  double t_prev = wall_seconds();
-  while (launched < total) {
-    const int cnt = std::min(chunk, total - launched);
-    for (int i = 0; i < cnt; ++i) {
-      st = launch_step(c, f, u);
-      if (st != MG_OK) return st;
-    }
-    launched += cnt;
-    MG_HIP(hipMemcpyAsync(&c->poll[2 * (k & 1)], &c->st->done, 2 * sizeof(int),
-                          hipMemcpyDeviceToHost, c->stream));
-    MG_HIP(hipEventRecord(c->ev[k & 1], c->stream));
-    if (!lookahead) {  // wait for this chunk (one step) at once
-      MG_HIP(hipEventSynchronize(c->ev[k & 1]));
-      if (c->poll[2 * (k & 1)] != 0) break;
-    } else if (k > 0) {
-      MG_HIP(hipEventSynchronize(c->ev[(k - 1) & 1]));
-      if (c->poll[2 * ((k - 1) & 1)] != 0) break;
-      // chunk k-1 ran from the end of chunk k-2 (or the start) to now
-      const double t = wall_seconds(), step_s = (t - t_prev) / std::max(prev_cnt, 1);
-      t_prev = t;
-      if (c->chunk == 0) {
-        if (step_s > kSyncStepSeconds) {
-          lookahead = false;
-          chunk = 1;
-        } else {
-          chunk = std::min(8, std::max(1, (int)std::ceil(kChunkSeconds / step_s)));
-        }
-      }
-    }
-    prev_cnt = cnt;
-    ++k;
+  for (int k = 0; k <= max_steps; ++k) {
+    st = launch_step(c, f, u);
+    if (st == MG_OK) st = wait_checks(c, k + 1);
+    if (st != MG_OK) return st;
+    if (c->mirror->done != 0) break;
   }
   mg_status outcome = MG_OK;
   st = fill_result(c, res, &outcome);
@@ -1045,6 +1022,20 @@ mg_status run(mg_ctx *c, const double *f, double *u, double rtol, int max_steps,
     g_error = res && res->floor_hit ? "solve stopped at the rounding floor above rtol"
                                     : "solve did not reach rtol";
   return outcome;
+}
+
+// Kernel launches of one solve step, roughly.
+int step_launches(const mg_ctx *c) {
+  const bool rb = c->cfg.smoother != MG_SMOOTH_JACOBI;
+  int per = 2;  // a level visit: one pass before and one after the coarse correction
+  if (c->dim == 2 && c->fused && rb)
+    per = rb_passes(&c->cfg);
+  else if (c->dim == 3 || !c->fused)
+    per = (rb ? 2 : 1) * (c->cfg.nu1 + c->cfg.nu2) + 2;
+  long total = 0, visits = 1;
+  for (int l = 0; l < c->L && l < c->tail_top && total < 1000; ++l, visits *= c->cfg.gamma) total += visits * per;
+  total += std::max(1L, visits / c->cfg.gamma);  // the tail or the coarsest solve
+  return (int)std::min(1000L, total * (c->cfg.precision == MG_PREC_MIXED ? c->cfg.inner_cycles : 1) + 3);
 }
 
 template <typename T>
@@ -1075,9 +1066,7 @@ mg_status mg_destroy(mg_handle h) {
   if (h->gexec) (void)hipGraphExecDestroy(h->gexec);
   if (h->graph) (void)hipGraphDestroy(h->graph);
   for (void *p : h->allocs) (void)hipFree(p);
-  if (h->poll) (void)hipHostFree(h->poll);
-  for (auto &e : h->ev)
-    if (e) (void)hipEventDestroy(e);
+  if (h->mirror) (void)hipHostFree(h->mirror);
   if (h->ev_async) (void)hipEventDestroy(h->ev_async);
   if (h->cap) (void)hipStreamDestroy(h->cap);
   delete h;
@@ -1102,7 +1091,6 @@ mg_status setup_ctx(const mg_config *cfg, void *hip_stream, int slots, bool own_
   c->omega = cfg->omega > 0.0 ? cfg->omega : default_omega(cfg->dim, cfg->order, cfg->smoother, cfg->coarse);
   c->stream = (hipStream_t)hip_stream;
   if (const char *g = std::getenv("MG_GRAPH")) c->use_graph = std::atoi(g) != 0;
-  if (const char *k = std::getenv("MG_CHUNK")) c->chunk = std::max(1, std::atoi(k));
   if (const char *fz = std::getenv("MG_FUSED")) c->fused = std::atoi(fz) != 0;
   if (cfg->smoother == MG_SMOOTH_JACOBI && (cfg->nu1 > 3 || cfg->nu2 > 2)) c->fused = false;
   // Gauss-Seidel partial steps and the cubic-adjoint restriction run as their own kernels on
@@ -1193,8 +1181,34 @@ mg_status setup_ctx(const mg_config *cfg, void *hip_stream, int slots, bool own_
         hipMemcpy(c->ecoef, coef.data(), coef.size() * sizeof(double), hipMemcpyHostToDevice) != hipSuccess)
       return bail(fail(MG_EDEVICE, "upload of the stencil entries failed"));
   }
-  // The coarse end of the hierarchy runs in one LDS-resident workgroup when it fits.
-  {
+  c->tail_top = L;
+  // 2D hierarchies that end in 9^2 take the kernel with compile-time sides, from 65^2 (FP64
+  // separable levels: 33^2) unless MG_TAIL_N sets a smaller top.  Measured against the
+  // general tail from 33^2 and two launches for 65^2: V(2,1) FP64 15.7 us against 25 + 13.
+  if (c->dim == 2 && c->ns[L - 1] == mgk::kTail2dCoarse && cfg->smoother != MG_SMOOTH_RBGS && cfg->restrict_op == 1) {
+    int cap = 65, lds_limit = 0;
+    if (const char *tn = std::getenv("MG_TAIL_N")) cap = std::atoi(tn);
+    if (hipDeviceGetAttribute(&lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device) != hipSuccess)
+      lds_limit = 65536;
+    int top = L - 1;
+    bool sep = false;
+    for (int l = L - 2; l >= 0 && c->ns[l] <= cap && c->ns[l] <= 65; --l) {
+      const bool sep_l = sep || !c->ops[l].cross;
+      const size_t need = mixed ? mgk::tail2d_lds_bytes<float>(c->ns[l], sep_l)
+                                : mgk::tail2d_lds_bytes<double>(c->ns[l], sep_l);
+      if (need > (size_t)lds_limit) break;
+      top = l;
+      sep = sep_l;
+    }
+    if (top < L - 1) {
+      hipError_t e = mixed ? mgk::tail2d_prepare<float>(c->ns[top], sep) : mgk::tail2d_prepare<double>(c->ns[top], sep);
+      if (e != hipSuccess) return bail(fail(MG_EDEVICE, std::string("tail setup: ") + hipGetErrorString(e)));
+      c->tail2d = true;
+      c->tail_top = top;
+    }
+  }
+  // The coarse end of any other hierarchy runs in one LDS-resident workgroup when it fits.
+  if (!c->tail2d) {
     int lds_limit = 0;
     if (hipDeviceGetAttribute(&lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device) != hipSuccess)
       lds_limit = 65536;
@@ -1219,31 +1233,6 @@ mg_status setup_ctx(const mg_config *cfg, void *hip_stream, int slots, bool own_
       hipError_t e = mixed ? mgk::tail_prepare<float>(c->dim, G, c->tail_lds)
                            : mgk::tail_prepare<double>(c->dim, G, c->tail_lds);
       if (e != hipSuccess) return bail(fail(MG_EDEVICE, std::string("tail setup: ") + hipGetErrorString(e)));
-    }
-  }
-  // 2D hierarchies that end in 9^2 take the kernel with compile-time sides, from 65^2 (FP64
-  // separable levels: 33^2) unless MG_TAIL_N sets a smaller top.  Measured against the
-  // general tail from 33^2 and two launches for 65^2: V(2,1) FP64 15.7 us against 25 + 13.
-  if (c->dim == 2 && c->ns[L - 1] == mgk::kTail2dCoarse && cfg->smoother != MG_SMOOTH_RBGS && cfg->restrict_op == 1) {
-    int cap = 65, lds_limit = 0;
-    if (const char *tn = std::getenv("MG_TAIL_N")) cap = std::atoi(tn);
-    if (hipDeviceGetAttribute(&lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device) != hipSuccess)
-      lds_limit = 65536;
-    int top = L - 1;
-    bool sep = false;
-    for (int l = L - 2; l >= 0 && c->ns[l] <= cap && c->ns[l] <= 65; --l) {
-      const bool sep_l = sep || !c->ops[l].cross;
-      const size_t need = mixed ? mgk::tail2d_lds_bytes<float>(c->ns[l], sep_l)
-                                : mgk::tail2d_lds_bytes<double>(c->ns[l], sep_l);
-      if (need > (size_t)lds_limit) break;
-      top = l;
-      sep = sep_l;
-    }
-    if (top < L - 1) {
-      hipError_t e = mixed ? mgk::tail2d_prepare<float>(c->ns[top], sep) : mgk::tail2d_prepare<double>(c->ns[top], sep);
-      if (e != hipSuccess) return bail(fail(MG_EDEVICE, std::string("tail setup: ") + hipGetErrorString(e)));
-      c->tail2d = true;
-      c->tail_top = top;
     }
   }
   if (c->dim == 3) {
@@ -1298,13 +1287,16 @@ mg_status setup_ctx(const mg_config *cfg, void *hip_stream, int slots, bool own_
     if (hipMemcpy(c->st, init.data(), sizeof(DevState) * slots, hipMemcpyHostToDevice) != hipSuccess)
       return bail(fail(MG_EDEVICE, "upload of the solve state failed"));
   }
-  if (hipHostMalloc((void **)&c->poll, 4 * sizeof(int), hipHostMallocDefault) != hipSuccess)
-    return bail(fail(MG_ENOMEM, "pinned host allocation failed"));
+  if (!own_top) {  // batches read their slots' states themselves
+    if (hipHostMalloc((void **)&c->mirror, sizeof(DevState), hipHostMallocDefault) != hipSuccess)
+      return bail(fail(MG_ENOMEM, "pinned host allocation failed"));
+    // Short steps are launched directly: a graph of a few kernels costs more than they do
+    // (65^2 FP64, 4 launches a step: 738 us as graphs, 614 direct; 65^3, 13: 2.50 and 2.39
+    // ms; 513^2 mixed, 31: 1.31 and 1.34 ms)
+    if (std::getenv("MG_GRAPH") == nullptr && step_launches(c) <= 16) c->use_graph = false;
+  }
   if (hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking) != hipSuccess)
     return bail(fail(MG_EDEVICE, "stream creation failed"));
-  for (auto &e : c->ev)
-    if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess)
-      return bail(fail(MG_EDEVICE, "event creation failed"));
   if (hipEventCreateWithFlags(&c->ev_async, hipEventDisableTiming) != hipSuccess)
     return bail(fail(MG_EDEVICE, "event creation failed"));
   *out = c;

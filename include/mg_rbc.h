@@ -36,8 +36,8 @@
  * gamma cycles on the next level from a zero guess (on the last level one exact solve by
  * the inverse formed at set-up), the correction interpolated with (1/4)]. 1 .; 1 4 1; . 1 .[ (C points copy, F
  * points take the mean of their four C neighbours) and added, nu2 sweeps.  The levels of
- * side <= 33 (environment MG_RBC_TAIL: another side, 0 for none) run in one workgroup
- * launch per visit; above them each half of a level's visit is one pass (environment
+ * side <= 33 (<= 65 where the last level is the standard 17^2 one; environment MG_RBC_TAIL:
+ * another side, 0 for none) run in one workgroup launch per visit; above them each half of a level's visit is one pass (environment
  * MG_RBC_PASSES=0: separate launches per step), with the same arithmetic.
  *
  * Status codes and mg_last_error() are those of mg.h.  Every call is asynchronous on the

@@ -330,14 +330,13 @@ __global__ __launch_bounds__(1024) void k_rbc_coarsest(const double *f, double *
 }
 
 // ------------------------------------------------------------- small-level tail ----
-// The levels from a side of at most 33 (by default) down to the coarsest run in one
-// 1024-thread workgroup: the same partial steps, interpolation and coarsest solve as the
-// per-level kernels (the same device functions), the restriction gathering each coarse
-// point's defects directly, one phase after another with a workgroup barrier between
-// them.  The small levels' arrays stay in the caches; the tail replaces a launch per
-// phase (five or six per level and visit) by a barrier.  Measured at 4097^2 (17 levels,
-// G1 V(1,1) cycle): 1.476 ms per-level, 1.456 ms from side 33, 1.477 ms from side 65 and
-// 1.662 ms from 129: a phase over a 65^2 level in one workgroup takes as long as a launch.
+// Hierarchies that do not end in the standard 17^2 level (rbc_tail.hip runs those) take the
+// levels from a side of at most 33 (by default) down to the coarsest in one 1024-thread
+// workgroup: the same partial steps, interpolation and coarsest solve as the per-level
+// kernels (the same device functions), the restriction gathering each coarse point's defects
+// directly, one phase after another with a workgroup barrier between them.  The small levels'
+// arrays stay in the caches; the tail replaces a launch per phase (five or six per level and
+// visit) by a barrier.
 constexpr int kTailMaxLevels = 8;
 
 struct TailLevel {
@@ -686,6 +685,8 @@ struct mg_rbc_ctx {
   double *ainv_t = nullptr;  // the coarsest operator's inverse, transposed (K x K)
   int *pos = nullptr;        // array index of each coarsest unknown
   int coarse_k = 0;
+  int tail_side = 0;         // 65 or 33: the tail runs resident in LDS from that side (rbc_tail.hip)
+  double *dst = nullptr;     // its sine table
   bool passes = true;        // levels of side >= 17 run as passes (rbc_passes.hip)
   int tail_top = 1 << 30;    // first level of the one-workgroup tail (none: past the last)
 };
@@ -756,9 +757,30 @@ mg_status launch_prolong(mg_rbc_ctx *h, int l, const double *ec, const double *u
 }
 
 // Levels tail_top .. last in one launch, the top level's arrays f and u, visited `visits`
-// times in a row.
-mg_status launch_tail(mg_rbc_ctx *h, const double *f, double *u, int visits, const int *done) {
+// times in a row; zero: u is the zero iterate (stored as well unless the tail is the
+// LDS-resident one).
+mg_status launch_tail(mg_rbc_ctx *h, const double *f, double *u, int visits, bool zero, const int *done) {
   const int top = h->tail_top, last = (int)h->lv.size() - 1;
+  const double omega = h->cfg.omega == 0.0 ? 1.0 : h->cfg.omega;
+  if (h->tail_side != 0) {
+    mgk::RbcTailArgs r{};
+    const int first = h->tail_side == 65 ? 0 : 2;
+    for (int i = 0; top + i < last; ++i) {
+      r.op[first + i] = h->lv[top + i].op;
+      r.om[first + i] = omega / h->lv[top + i].op.c0;
+    }
+    r.gamma = h->cfg.gamma;
+    r.nu1 = h->cfg.nu1;
+    r.nu2 = h->cfg.nu2;
+    r.visits = visits;
+    r.zero = zero ? 1 : 0;
+    r.f = f;
+    r.u = u;
+    r.dst = h->dst;
+    r.done = done;
+    RBC_HIP(mgk::launch_rbc_tail(h->tail_side, r, h->stream));
+    return MG_OK;
+  }
   TailArgs a{};
   a.nl = last - top + 1;
   for (int i = 0; i < a.nl; ++i) {
@@ -770,7 +792,7 @@ mg_status launch_tail(mg_rbc_ctx *h, const double *f, double *u, int visits, con
   a.nu1 = h->cfg.nu1;
   a.nu2 = h->cfg.nu2;
   a.visits = visits;
-  a.omega = h->cfg.omega == 0.0 ? 1.0 : h->cfg.omega;
+  a.omega = omega;
   a.ainv_t = h->ainv_t;
   a.pos = h->pos;
   a.K = h->coarse_k;
@@ -819,8 +841,16 @@ mg_status visits(mg_rbc_ctx *h, int l, const int *done) {
   const int last = (int)h->lv.size() - 1;
   const int reps = l + 1 < last ? h->cfg.gamma : 1;
   if (l + 1 == h->tail_top)  // the visits of the tail's top level in one launch
-    return launch_tail(h, h->f[l + 1], h->u[l + 1], reps, done);
+    return launch_tail(h, h->f[l + 1], h->u[l + 1], reps, true, done);
   for (int k = 0; k < reps; ++k) RBC_TRY(cycle(h, l + 1, h->f[l + 1], h->u[l + 1], k == 0, false, done));
+  return MG_OK;
+}
+
+mg_status launch_check(mg_rbc_ctx *h, int np) {
+  const double ni = (double)(h->lv[0].m - 2) * (double)(h->lv[0].m - 2);
+  hipLaunchKernelGGL(k_rbc_check, dim3(1), dim3(256), 0, h->stream, h->state, h->host, h->partial, np, 1.0 / ni,
+                     h->cfg.rtol, h->cfg.max_cycles);
+  RBC_HIP(hipGetLastError());
   return MG_OK;
 }
 
@@ -835,7 +865,8 @@ mg_status cycle_passes(mg_rbc_ctx *h, int l, const double *f, double *u, bool ze
     return o == in ? h->t2[l] : o;
   };
   // the next level's iterate has to be zeros only where its first step reads it
-  double *uc = pass_level(h, l + 1) ? nullptr : h->u[l + 1];
+  const bool lds_tail = h->tail_side != 0 && l + 1 == h->tail_top;
+  double *uc = pass_level(h, l + 1) || lds_tail ? nullptr : h->u[l + 1];
   for (; k < h->cfg.nu1; ++k) {
     const bool last = k == h->cfg.nu1 - 1;
     double *o = target();
@@ -843,12 +874,7 @@ mg_status cycle_passes(mg_rbc_ctx *h, int l, const double *f, double *u, bool ze
     RBC_HIP(mgk::launch_rbc_pre(L.odd, L.op, omega, f, in, o, last ? h->f[l + 1] : nullptr, last ? uc : nullptr,
                                 L.m, check && k == 0 ? h->partial : nullptr, &np, done, h->stream));
     in = o;
-    if (check && k == 0) {
-      const double ni = (double)(L.m - 2) * (double)(L.m - 2);
-      hipLaunchKernelGGL(k_rbc_check, dim3(1), dim3(256), 0, h->stream, h->state, h->host, h->partial, np,
-                         1.0 / ni, h->cfg.rtol, h->cfg.max_cycles);
-      RBC_HIP(hipGetLastError());
-    }
+    if (check && k == 0) RBC_TRY(launch_check(h, np));
   }
   RBC_TRY(visits(h, l, done));
   for (int j = 0; j < h->cfg.nu2; ++j, ++k) {
@@ -863,12 +889,27 @@ mg_status cycle_passes(mg_rbc_ctx *h, int l, const double *f, double *u, bool ze
   return in == u ? MG_OK : fail(MG_EDEVICE, "sweep targets out of order");
 }
 
+// Partial sums of the squared residual of level 0; returns their number.
+int launch_norm(mg_rbc_ctx *h, const double *f, const double *u) {
+  const Level &L = h->lv[0];
+  const int blocks = std::min(kNormBlocks, L.m - 2);  // a block takes whole interior rows
+  hipLaunchKernelGGL(k_rbc_resnorm, dim3(blocks), dim3(256), 0, h->stream, f, u, L.m, L.op, h->partial);
+  return blocks;
+}
+
 // One cycle from level l (zero: from the zero iterate, which u then holds unless the level
 // runs as passes).  check, done: a solve's first pass forms the residual norm, and every
 // launch returns at once when *done is set (passes on every level above the tail only).
 mg_status cycle(mg_rbc_ctx *h, int l, const double *f, double *u, bool zero, bool check, const int *done) {
   const int last = (int)h->lv.size() - 1;
-  if (l == h->tail_top) return launch_tail(h, f, u, 1, done);
+  if (l == h->tail_top) {
+    if (check) {  // the whole cycle is the tail: a pass for the norm
+      const int blocks = launch_norm(h, f, u);
+      RBC_HIP(hipGetLastError());
+      RBC_TRY(launch_check(h, blocks));
+    }
+    return launch_tail(h, f, u, 1, zero, done);
+  }
   if (l == last) return launch_coarsest(h, f, u, done);
   if (pass_level(h, l)) return cycle_passes(h, l, f, u, zero, check, done);
   for (int k = 0; k < h->cfg.nu1; ++k) RBC_TRY(sweep(h, l, f, u));
@@ -882,8 +923,7 @@ mg_status cycle(mg_rbc_ctx *h, int l, const double *f, double *u, bool zero, boo
 mg_status norm(mg_rbc_ctx *h, const double *f, const double *u, double *out) {
   const Level &L = h->lv[0];
   const size_t ni = (size_t)(L.m - 2) * (L.m - 2);
-  const int blocks = std::min(kNormBlocks, L.m - 2);  // a block takes whole interior rows
-  hipLaunchKernelGGL(k_rbc_resnorm, dim3(blocks), dim3(256), 0, h->stream, f, u, L.m, L.op, h->partial);
+  const int blocks = launch_norm(h, f, u);
   RBC_HIP(hipGetLastError());
   hipLaunchKernelGGL(k_rbc_sum, dim3(1), dim3(256), 0, h->stream, h->partial, blocks, 1.0 / (double)ni,
                      h->norm_dev);
@@ -898,7 +938,7 @@ mg_status norm(mg_rbc_ctx *h, const double *f, const double *u, double *out) {
 // its checks): passes on every level above the tail or the coarsest level.
 bool solve_on_device(const mg_rbc_ctx *h) {
   const int below = std::min((int)h->lv.size() - 1, h->tail_top);
-  if (below == 0) return false;
+  if (below == 0) return h->tail_side != 0;
   for (int l = 0; l < below; ++l)
     if (!pass_level(h, l)) return false;
   return true;
@@ -1013,14 +1053,34 @@ mg_status mg_rbc_setup(const mg_rbc_config *cfg, void *stream, mg_rbc_ctx **out)
   }
   // the one-workgroup tail: from the first level of side <= MG_RBC_TAIL (default 33; 0
   // switches it off) to the coarsest, at least two levels and at most kTailMaxLevels
+  // hierarchies that end in the standard 17^2 level run it resident in LDS, from side 65
   {
     const char *e = getenv("MG_RBC_TAIL");
-    const int side = e != nullptr && *e != 0 ? atoi(e) : 33;
     const int last = cfg->levels - 1;
+    const bool to17 = last % 2 == 0 && h->lv[last].m == 17;
+    const int side = e != nullptr && *e != 0 ? atoi(e) : to17 ? 65 : 33;
     int top = 0;
     while (top <= last && h->lv[top].m > side) ++top;
     top = std::max(top, last + 1 - kTailMaxLevels);
     if (side > 0 && top < last) h->tail_top = top;
+    const int m = top < last ? h->lv[top].m : 0;
+    int dev = 0, lds = 0;
+    if (h->tail_top == top && to17 && !h->lv[top].odd && (m == 65 || m == 33) && hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess &&
+        mgk::rbc_tail_lds(m) <= (size_t)lds) {
+      const std::vector<double> tab = mgk::rbc_tail_table(h->lv[last].op);
+      if (!alloc(&h->dst, tab.size())) {
+        mg_rbc_destroy(h);
+        return fail(MG_ENOMEM, "device allocation failed");
+      }
+      hipError_t er = hipMemcpy(h->dst, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice);
+      if (er == hipSuccess) er = mgk::rbc_tail_prepare(m);
+      if (er != hipSuccess) {
+        mg_rbc_destroy(h);
+        return fail(MG_EDEVICE, std::string("tail setup: ") + hipGetErrorString(er));
+      }
+      h->tail_side = m;
+    }
   }
   // every level array starts at zero: their boundaries and off-grid entries stay zero
   for (int l = 1; l < cfg->levels; ++l) {
@@ -1054,6 +1114,7 @@ void mg_rbc_destroy(mg_rbc_ctx *h) {
   release(h->partial);
   release(h->norm_dev);
   release(h->ainv_t);
+  release(h->dst);
   if (h->pos) (void)hipFree(h->pos);
   if (h->norm_host) (void)hipHostFree(h->norm_host);
   delete h;

@@ -77,3 +77,51 @@ def test_solve_from_zero_and_nonfinite_data():
         assert (st, k) == (mg.MG_OK, 0) and not np.isfinite(hist[0])
     finally:
         P.close()
+
+
+TAIL_CASES = [
+    # n, levels (the last one 17^2), coarse, gamma, nu1, nu2, omega
+    (33, 3, "G1", 1, 1, 1, 1.0), (33, 3, "NG", 2, 2, 1, 1.2), (65, 5, "G1", 2, 1, 1, 1.0), (65, 5, "NG", 1, 0, 2, 1.0),
+    (65, 5, "GN", 1, 2, 0, 0.9), (129, 7, "G1", 2, 2, 2, 1.1), (257, 9, "NG", 2, 1, 1, 1.0), (513, 11, "G1", 1, 1, 2, 1.0),
+]
+
+
+@pytest.mark.parametrize("side", ["33", "65"])
+@pytest.mark.parametrize("n,levels,coarse,gamma,nu1,nu2,omega", TAIL_CASES)
+def test_lds_tail_equals_per_level_kernels(n, levels, coarse, gamma, nu1, nu2, omega, side, monkeypatch):
+    """The tail resident in LDS (hierarchies that end in the standard 17^2 level) against the
+    separate kernels down to the dense coarsest solve; with n = 33 and 65 the whole cycle is
+    the tail, Dirichlet values in u and junk in f's boundary included."""
+    f, u0 = _grid(n, 60 + n) * (n - 1) ** 2, _grid(n, 61 + n)
+    u0[0, :], u0[-1, :], u0[:, 0], u0[:, -1] = 0.5, np.linspace(0.5, 2.0, n), 0.25, np.linspace(1.0, 0.0, n)
+    f[0, :] = f[:, 0] = f[-1, :] = f[:, -1] = np.nan
+    out = []
+    monkeypatch.setenv("MG_RBC_PASSES", "0")
+    for env in ("0", side):
+        monkeypatch.setenv("MG_RBC_TAIL", env)
+        P = Pair(n, levels, coarse, gamma, nu1, nu2, omega)
+        try:
+            fd, ud = dev(f), dev(u0)
+            rbc.cycles(P.h, fd.data_ptr(), ud.data_ptr(), 2)
+            out.append(host(ud))
+        finally:
+            P.close()
+    _close(out[1], out[0], "tail against separate kernels")
+    for edge in (np.s_[0, :], np.s_[-1, :], np.s_[:, 0], np.s_[:, -1]):
+        assert np.array_equal(out[1][edge], u0[edge])
+
+
+def test_solve_whose_cycle_is_the_tail():
+    """n = 65 with the 17^2 coarsest level: every cycle one launch, checks on the device."""
+    P = Pair(65, 5, "G1", 1, 1, 1, 1.0, max_cycles=40)
+    try:
+        f = _grid(65, 77) * 64.0 ** 2
+        fd, ud = dev(f), dev(np.zeros((65, 65)))
+        st, k, hist = rbc.solve(P.h, fd.data_ptr(), ud.data_ptr(), 40)
+        assert st == mg.MG_OK and len(hist) == k + 1 and hist[-1] <= 1e-10 * hist[0] < hist[-2]
+        u = np.zeros((65, 65))
+        for _ in range(k):
+            u = P.o.cycle(f, u)
+        _close(host(ud), u, "solution")
+    finally:
+        P.close()

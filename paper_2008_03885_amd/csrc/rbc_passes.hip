@@ -31,7 +31,6 @@ namespace {
 constexpr int kWave = 64, kWaves = kBlock / kWave;
 constexpr int kAhead = 4;  // rows of every array in flight
 constexpr int kTurn = 8;   // row steps per unrolled loop turn: the length of the rings
-constexpr int kMinRows = 4;
 
 __device__ __forceinline__ int dpp_prev(int v) { return __builtin_amdgcn_mov_dpp(v, 0x138, 0xf, 0xf, true); }
 __device__ __forceinline__ int dpp_next(int v) { return __builtin_amdgcn_mov_dpp(v, 0x130, 0xf, 0xf, true); }
@@ -476,11 +475,31 @@ __global__ __launch_bounds__(kBlock) void k_rbc_post_rot(PassArgs a) {
 
 int cdiv(int a, int b) { return (a + b - 1) / b; }
 
-// Blocks across, and bands that fill one round of resident blocks.
+// Rows per band.  A band of r rows marches r + extra row steps in turns of kTurn, so r =
+// kTurn j - extra; the band with the fewest turns times rounds of resident blocks, and of
+// those the one with the least work in all.  (One round in bands of at least four rows took
+// 8.4 us for a post pass over a 129^2 rotated level, 16 steps; two rows, 8 steps, 6.6 us.)
+int pass_rows(int rows, int across, int capacity, int extra) {
+  int best = 0;
+  long cost0 = 0, work0 = 0;
+  for (int r = kTurn - extra % kTurn; r < rows + kTurn; r += kTurn) {
+    if (r < 2) continue;
+    const long blocks = (long)across * cdiv(rows, r), steps = r + extra;
+    const long cost = (blocks + capacity - 1) / capacity * steps, work = blocks * steps;
+    if (best == 0 || cost < cost0 || (cost == cost0 && work < work0)) {
+      best = r;
+      cost0 = cost;
+      work0 = work;
+    }
+  }
+  return best;
+}
+
+// Blocks across and bands; extra: row steps of a band beyond its rows.
 template <typename K>
-hipError_t launch(K kernel, PassArgs &a, int cols, int H, int *np, hipStream_t s) {
+hipError_t launch(K kernel, PassArgs &a, int cols, int H, int extra, int *np, hipStream_t s) {
   dim3 grid(cdiv(cdiv(cols, kWave - 2 * H), kWaves));
-  a.chunk = band_rows(cols, grid.x, resident_blocks((const void *)kernel, kBlock, 0), kMinRows);
+  a.chunk = pass_rows(cols, grid.x, resident_blocks((const void *)kernel, kBlock, 0), extra);
   grid.y = cdiv(cols, a.chunk);
   if (np) *np = grid.x * grid.y;
   hipLaunchKernelGGL(kernel, grid, dim3(kBlock), 0, s, a);
@@ -489,7 +508,8 @@ hipError_t launch(K kernel, PassArgs &a, int cols, int H, int *np, hipStream_t s
 
 }  // namespace
 
-int rbc_pre_partials(int m) { return cdiv(cdiv(m, kWave - 8), kWaves) * cdiv(m, kMinRows); }
+// Bands of a standard level have at least five rows (pass_rows with extra 3 or 9).
+int rbc_pre_partials(int m) { return cdiv(cdiv(m, kWave - 8), kWaves) * cdiv(m, 5); }
 
 hipError_t launch_rbc_pre(bool odd, const RbcOp &op, double omega, const double *f, const double *u,
                           double *uout, double *fc, double *uc, int m, double *partials, int *np,
@@ -497,12 +517,13 @@ hipError_t launch_rbc_pre(bool odd, const RbcOp &op, double omega, const double 
   if (m < kRbcPassSide || uout == u || uout == nullptr || f == nullptr) return hipErrorInvalidValue;
   PassArgs a{f, u, nullptr, uout, fc, uc, m, 0, op, omega / op.c0, odd ? nullptr : partials, done};
   const int cols = odd ? (m + 1) / 2 : m, H = fc != nullptr ? 4 : 2;
+  const int extra = fc != nullptr ? (odd ? 6 : 9) : (odd ? 2 : 3);
   const bool wide = odd ? op.a2 != 0.0 : op.d1 != 0.0;
 #define RBC_PRE(K, W)                                                                                        \
-  return fc != nullptr ? (u != nullptr ? launch(K<W, true, true>, a, cols, H, np, s)                         \
-                                       : launch(K<W, false, true>, a, cols, H, np, s))                       \
-                       : (u != nullptr ? launch(K<W, true, false>, a, cols, H, np, s)                        \
-                                       : launch(K<W, false, false>, a, cols, H, np, s))
+  return fc != nullptr ? (u != nullptr ? launch(K<W, true, true>, a, cols, H, extra, np, s)                         \
+                                       : launch(K<W, false, true>, a, cols, H, extra, np, s))                       \
+                       : (u != nullptr ? launch(K<W, true, false>, a, cols, H, extra, np, s)                        \
+                                       : launch(K<W, false, false>, a, cols, H, extra, np, s))
   if (odd) {
     if (wide) RBC_PRE(k_rbc_pre_rot, true);
     RBC_PRE(k_rbc_pre_rot, false);
@@ -519,10 +540,10 @@ hipError_t launch_rbc_post(bool odd, const RbcOp &op, double omega, const double
   PassArgs a{f, uin, e, uout, nullptr, nullptr, m, 0, op, omega / op.c0, nullptr, done};
   const int cols = odd ? (m + 1) / 2 : m;
   if (odd)
-    return op.a2 != 0.0 ? launch(k_rbc_post_rot<true>, a, cols, 3, nullptr, s)
-                        : launch(k_rbc_post_rot<false>, a, cols, 3, nullptr, s);
-  return op.d1 != 0.0 ? launch(k_rbc_post_std<true>, a, cols, 3, nullptr, s)
-                      : launch(k_rbc_post_std<false>, a, cols, 3, nullptr, s);
+    return op.a2 != 0.0 ? launch(k_rbc_post_rot<true>, a, cols, 3, 6, nullptr, s)
+                        : launch(k_rbc_post_rot<false>, a, cols, 3, 6, nullptr, s);
+  return op.d1 != 0.0 ? launch(k_rbc_post_std<true>, a, cols, 3, 6, nullptr, s)
+                      : launch(k_rbc_post_std<false>, a, cols, 3, 6, nullptr, s);
 }
 
 }  // namespace mgk

@@ -71,56 +71,6 @@ __device__ __forceinline__ int fold(int i, int n, int &sign) {
 
 __device__ __forceinline__ void wave_sync() { __builtin_amdgcn_wave_barrier(); }
 
-// L u at the centre of window w (rows c-R..c+R of this lane's column); x neighbours
-// through the wave's LDS rows (ra, rb point at this lane's slot).  Cross operator
-// (R = 2, or R = 3 with XC): difference form with weights w1, w2 (, w3).  Separable
-// operator (R = 3): L = a_x b_y + b_x a_y with the a factors in difference form.
-template <typename T, int R, bool XC = false>
-__device__ __forceinline__ T apply_op(const T (&w)[2 * R + 1], const KOp<T> &op, T *ra, T *rb) {
-  const T c = w[R];
-  if constexpr (XC) {
-    ra[0] = c;
-    wave_sync();
-    const T xm1 = ra[-1], xp1 = ra[1], xm2 = ra[-2], xp2 = ra[2], xm3 = ra[-3], xp3 = ra[3];
-    wave_sync();
-    return op.w1 * (((c - xm1) + (c - xp1)) + ((c - w[R - 1]) + (c - w[R + 1]))) +
-           op.w2 * (((c - xm2) + (c - xp2)) + ((c - w[R - 2]) + (c - w[R + 2]))) +
-           op.w3 * (((c - xm3) + (c - xp3)) + ((c - w[R - 3]) + (c - w[R + 3])));
-  } else if constexpr (R == 2) {
-    ra[0] = c;
-    wave_sync();
-    const T xm1 = ra[-1], xp1 = ra[1], xm2 = ra[-2], xp2 = ra[2];
-    wave_sync();
-    return op.w1 * (((c - xm1) + (c - xp1)) + ((c - w[R - 1]) + (c - w[R + 1]))) +
-           op.w2 * (((c - xm2) + (c - xp2)) + ((c - w[R - 2]) + (c - w[R + 2])));
-  } else {
-    T A = T(0), B = T(0);
-#pragma unroll
-    for (int k = 0; k < 2 * R + 1; ++k) {
-      if (k != R) A += op.a[k] * (w[k] - c);
-      B += op.b[k] * w[k];
-    }
-    ra[0] = A;
-    rb[0] = B;
-    wave_sync();
-    T lu = T(0);
-#pragma unroll
-    for (int i = 0; i < 2 * R + 1; ++i) {
-      if (i != R) lu += op.a[i] * (rb[i - R] - B);
-      lu += op.b[i] * ra[i - R];
-    }
-    wave_sync();
-    return lu;
-  }
-}
-
-template <typename T, int N>
-__device__ __forceinline__ void push(T (&w)[N], T v) {
-#pragma unroll
-  for (int k = 0; k < N - 1; ++k) w[k] = w[k + 1];
-  w[N - 1] = v;
-}
-
 __device__ double block_sum(double v) {
   __shared__ double ws[kWavesPerBlock];
   for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
@@ -457,13 +407,27 @@ struct PostArgs {
   const int *done;
 };
 
+// Stage s (1 <= s <= NU2) works on row t - s (R+1) at row step t, the corrected iterate on
+// row t: every stage reads only values of earlier row steps, and all exchanges of a row step
+// (the stages' and, on even rows, the new coarse row's) go through LDS together.  As in the
+// pre kernel every carried value sits in a ring that the loop, unrolled by kTurnPost row
+// steps, addresses at compile time, so loads stay in flight; the first row step of a band is
+// on an even row.  (With queues shifted by a register move per row each step waited for the
+// loads of the step before.  Averages in a 4097^2 FP64 V(2,1) solve, both with their bands:
+// level 0 94 -> 97 us, at the traffic limit either way, 1025^2 12.6 -> 10.8 us.)
+constexpr int kTurnPost = 8;
 template <typename T, int R, int NU2, int P, bool RBS = false, bool XC = false>
 __global__ __launch_bounds__(kBlock) void k_post2d(PostArgs<T> a) {
   constexpr int H = NU2 * R;
   constexpr int S = kWave - 2 * H;
   constexpr int W = 2 * R + 1;
-  constexpr int FQ = NU2 > 0 ? (NU2 - 1) * R + 1 : 1;
-  __shared__ T lrow[kWavesPerBlock][2][kRowLen];
+  constexpr int LAG = R + 1;
+  constexpr int LR = kTurnPost;
+  constexpr bool CROSS = R == 2 || XC;
+  constexpr int XV = CROSS ? 1 : 2;   // values one stage exchanges across lanes
+  constexpr int NX = NU2 * XV + 1;    // LDS rows per wave; the last one for the coarse row
+  static_assert(LAG + R < LR && LR % kPF == 0 && kPF == 4, "rings hold a stage's rows; queues divide");
+  __shared__ T lrow[kWavesPerBlock][NX][kRowLen];
   a.done = slot_done(a.done);
   if (stopped(a.done)) return;
   const int n = a.n, nc = (n - 1) / 2 + 1;
@@ -479,8 +443,7 @@ __global__ __launch_bounds__(kBlock) void k_post2d(PostArgs<T> a) {
   const int x = x0 + lane;
   if (strip * S >= n) return;  // whole wave idle; no block barrier follows
   const bool useful = lane >= H && lane < H + S && x <= n - 1;
-  T *ra = &lrow[wv][0][kPad + lane];
-  T *rb = &lrow[wv][1][kPad + lane];
+  T *const lds0 = &lrow[wv][0][kPad + lane];
   Column<T> col;
   col.init(x, n);
   // coarse column loaded by this lane (lanes 0..35 cover the strip and its stencil)
@@ -489,90 +452,153 @@ __global__ __launch_bounds__(kBlock) void k_post2d(PostArgs<T> a) {
   ccol.init(Ib + lane, nc);
   // LDS slots of this fine column's coarse neighbours (relative to the lane's own slot)
   const int src0 = floordiv2(x) - Ib - lane;
-  T *crow = &lrow[wv][1][kPad + lane];
+  T *const crow = lds0 + (NX - 1) * kRowLen;
 
   const int y0 = blk.y * a.chunk;
   const int y1 = min(y0 + a.chunk, n);
-  const int ts = y0 - NU2 * R, te = y1 - 1 + NU2 * R;
-  const int jb0 = floordiv2(ts) - 1;
-  const bool fast = ts - R > 0 && te + kPF < n - 1 && jb0 - 1 > 0 && floordiv2(te) + 4 < nc - 1;
+  const int ts = 2 * floordiv2(y0 - NU2 * R);
+  const int te = ts + round_up(y1 - 1 + NU2 * LAG - ts + 1, LR) - 1;
+  const int jb0 = ts / 2;  // ts is even (it may be negative)
+  const bool fast = ts - LAG > 0 && te + kPF < n - 1 && jb0 - 1 > 0 && te / 2 + 5 < nc - 1;
   const T *fp = NU2 > 0 ? a.f : a.uin;  // f is not read without post-smoothing
 
   auto run = [&](auto fast_tag) {
     constexpr bool FAST = decltype(fast_tag)::value;
-    // x-interpolation of a coarse row at this lane's fine column
-    auto interp = [&](T cv) -> T {
-      crow[0] = cv;
-      wave_sync();
+    // x-interpolation at this lane's fine column from the coarse row in crow
+    auto interp = [&]() -> T {
       const T c0 = crow[src0], c1 = crow[src0 + 1];
-      T out;
       if (P == 3) {
         const T cm = crow[src0 - 1], c2 = crow[src0 + 2];
-        out = (x & 1) == 0 ? c0 : (T(9) * (c0 + c1) - (cm + c2)) * T(0.0625);
-      } else {
-        out = (x & 1) == 0 ? c0 : T(0.5) * (c0 + c1);
+        return (x & 1) == 0 ? c0 : (T(9) * (c0 + c1) - (cm + c2)) * T(0.0625);
       }
-      wave_sync();
-      return out;
+      return (x & 1) == 0 ? c0 : T(0.5) * (c0 + c1);
     };
+    auto coarse = [&](int J) { return a.v[ccol.template addr<FAST>(J)]; };
+    // interpolated coarse row J in slot J - jb0 + 1 mod 4: rows jb0-1 .. jb0+1 now, row
+    // t/2 + 2 at every even row step t
     T pw[4];
-    int jb = jb0;
-    // coarse rows jb..jb+3 now, and the next one ahead
+    pw[3] = T(0);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) pw[k] = interp(ccol.template fix<FAST>(a.v[ccol.template addr<FAST>(jb + k)], jb + k));
-    T cnext = a.v[ccol.template addr<FAST>(jb + 4)];
-    T w[NU2 + 1][W];
+    for (int k = 0; k < 3; ++k) {
+      crow[0] = ccol.template fix<FAST>(coarse(jb0 - 1 + k), jb0 - 1 + k);
+      wave_sync();
+      pw[k] = interp();
+      wave_sync();
+    }
+    // w[s]: stage-s rows (0: the corrected iterate), slot (row - ts) mod LR
+    T w[NU2 + 1][LR], fr[LR];
 #pragma unroll
     for (int s = 0; s <= NU2; ++s)
 #pragma unroll
-      for (int k = 0; k < W; ++k) w[s][k] = T(0);
-    T fw[FQ];
+      for (int k = 0; k < LR; ++k) w[s][k] = T(0);
 #pragma unroll
-    for (int k = 0; k < FQ; ++k) fw[k] = T(0);
-    T uq[kPF], fq[kPF];
+    for (int k = 0; k < LR; ++k) fr[k] = T(0);
+    // loads in flight: u of row t, f of row t - LAG, the coarse row t/2 + 2
+    T uq[kPF], fq[kPF], cq[2];
 #pragma unroll
     for (int p = 0; p < kPF; ++p) {
       uq[p] = a.uin[col.template addr<FAST>(ts + p)];
-      if (NU2 > 0) fq[p] = fp[col.template addr<FAST>(ts - R + p)];
+      if (NU2 > 0) fq[p] = fp[col.template addr<FAST>(ts - LAG + p)];
     }
+    cq[0] = coarse(jb0 + 2);
+    cq[1] = coarse(jb0 + 3);
     const KOp<T> op = a.op;
 
-    for (int t = ts; t <= te; ++t) {
-      const int Jc = floordiv2(t);
-      if (jb < Jc - 1) {  // the stencil moved down one coarse row (every other fine row)
-        const T nv = interp(ccol.template fix<FAST>(cnext, jb + 4));
-        cnext = a.v[ccol.template addr<FAST>(jb + 5)];
-        push(pw, nv);
-        ++jb;
-      }
-      const T pv = ((t & 1) == 0) ? pw[1]
-                   : (P == 3 ? (T(9) * (pw[1] + pw[2]) - (pw[0] + pw[3])) * T(0.0625)
-                             : T(0.5) * (pw[1] + pw[2]));
-      const T unew = col.template fix<FAST>(uq[0], t);
-      push(uq, a.uin[col.template addr<FAST>(t + kPF)]);
-      const T ut = unew + pv;  // corrected iterate at row t
-      T out = ut;
-      int c = t;
-      if (NU2 > 0) {
-        const T fnew = col.template fix<FAST>(fq[0], t - R);
-        push(fq, fp[col.template addr<FAST>(t - R + kPF)]);
-        push(fw, fnew);
-        push(w[0], ut);
+    // Row step t = ts + (multiple of LR) + Pt.
+    auto step = [&](const int t, auto pc) {
+      constexpr int Pt = decltype(pc)::value;
+      constexpr int Q = Pt % kPF, K = Pt / 2;  // K: coarse rows advanced within the turn
+      constexpr bool EVEN = Pt % 2 == 0;
+      T unew = col.template fix<FAST>(uq[Q], t);
+      T fnew = NU2 > 0 ? col.template fix<FAST>(fq[Q], t - LAG) : T(0);
+      T cnew = EVEN ? ccol.template fix<FAST>(cq[K % 2], t / 2 + 2) : T(0);
+      asm volatile("" : "+v"(unew), "+v"(fnew), "+v"(cnew));
+      __builtin_amdgcn_sched_barrier(0);
+      uq[Q] = a.uin[col.template addr<FAST>(t + kPF)];
+      if (NU2 > 0) fq[Q] = fp[col.template addr<FAST>(t - LAG + kPF)];
+      if (EVEN) cq[K % 2] = coarse(t / 2 + 4);
+      fr[ring<LR>(Pt - LAG)] = fnew;
+      // one exchange for every stage and the coarse row
+      T ya_[NU2 > 0 ? NU2 : 1], yb_[NU2 > 0 ? NU2 : 1];
 #pragma unroll
-        for (int s = 1; s <= NU2; ++s) {
-          // stage s: sweep at row t - s R, the centre of w[s-1]
-          const T fv = fw[FQ - 1 - (s - 1) * R];
-          const T r = fv - apply_op<T, R, XC>(w[s - 1], op, ra, rb);
-          push(w[s], w[s - 1][R] + (RBS ? stage_om(op, s, x + t - s * R) : op.om_d) * r);
+      for (int s = 1; s <= NU2; ++s) {
+        if constexpr (CROSS) {
+          ya_[s - 1] = w[s - 1][ring<LR>(Pt - s * LAG)];
+          lds0[(s - 1) * kRowLen] = ya_[s - 1];
+        } else {
+          const T c = w[s - 1][ring<LR>(Pt - s * LAG)];
+          T A = T(0), B = T(0);
+#pragma unroll
+          for (int k = 0; k < W; ++k) {
+            const T v = w[s - 1][ring<LR>(Pt - s * LAG + k - R)];
+            if (k != R) A += op.a[k] * (v - c);
+            B += op.b[k] * v;
+          }
+          ya_[s - 1] = A;
+          yb_[s - 1] = B;
+          lds0[(2 * s - 2) * kRowLen] = A;
+          lds0[(2 * s - 1) * kRowLen] = B;
         }
-        out = w[NU2][W - 1];
-        c = t - NU2 * R;
       }
+      if (EVEN) crow[0] = cnew;
+      wave_sync();
+      T lu[NU2 > 0 ? NU2 : 1];
+#pragma unroll
+      for (int s = 1; s <= NU2; ++s) {
+        if constexpr (CROSS) {
+          const T *row = lds0 + (s - 1) * kRowLen;
+          const T c = ya_[s - 1];
+          T d[3];
+#pragma unroll
+          for (int k = 1; k <= R; ++k) {
+            const T ym = w[s - 1][ring<LR>(Pt - s * LAG - k)], yp = w[s - 1][ring<LR>(Pt - s * LAG + k)];
+            d[k - 1] = ((c - row[-k]) + (c - row[k])) + ((c - ym) + (c - yp));
+          }
+          lu[s - 1] = op.w1 * d[0] + op.w2 * d[1];
+          if (R == 3) lu[s - 1] += op.w3 * d[R - 1];
+        } else {
+          const T *ra = lds0 + (2 * s - 2) * kRowLen;
+          const T *rb = lds0 + (2 * s - 1) * kRowLen;
+          const T B = yb_[s - 1];
+          T v = T(0);
+#pragma unroll
+          for (int i = 0; i < W; ++i) {
+            if (i != R) v += op.a[i] * (rb[i - R] - B);
+            v += op.b[i] * ra[i - R];
+          }
+          lu[s - 1] = v;
+        }
+      }
+      T cint = EVEN ? interp() : T(0);
+      wave_sync();
+      // rows t/2 - 1 .. t/2 + 2 sit in slots K .. K + 3 (mod 4); the last one arrives now
+      if (EVEN) pw[(K + 3) % 4] = cint;
+      T pv;
+      if (EVEN)
+        pv = pw[(K + 1) % 4];
+      else
+        pv = P == 3 ? (T(9) * (pw[(K + 1) % 4] + pw[(K + 2) % 4]) - (pw[K % 4] + pw[(K + 3) % 4])) * T(0.0625)
+                    : T(0.5) * (pw[(K + 1) % 4] + pw[(K + 2) % 4]);
+      const T ut = unew + pv;  // corrected iterate at row t
+      T nv[NU2 > 0 ? NU2 : 1];
+#pragma unroll
+      for (int s = 1; s <= NU2; ++s) {
+        const int row = t - s * LAG;
+        const T r = fr[ring<LR>(Pt - s * LAG)] - lu[s - 1];
+        nv[s - 1] = w[s - 1][ring<LR>(Pt - s * LAG)] + (RBS ? stage_om(op, s, x + row) : op.om_d) * r;
+      }
+      const T out = NU2 > 0 ? nv[NU2 > 0 ? NU2 - 1 : 0] : ut;
+      const int c = t - NU2 * LAG;
       if (useful && c >= y0 && c < y1) {
         const bool inside = col.xin && c > 0 && c < n - 1;
         a.uout[(size_t)c * n + x] = inside ? out : T(0);
       }
-    }
+      w[0][ring<LR>(Pt)] = ut;
+#pragma unroll
+      for (int s = 1; s < NU2; ++s) w[s][ring<LR>(Pt - s * LAG)] = nv[s - 1];
+    };
+    for (int t = ts; t <= te; t += LR)
+      static_for<LR>([&](auto pc) { step(t + decltype(pc)::value, pc); });
   };
   if (fast)
     run(std::true_type{});
@@ -597,24 +623,44 @@ KOp<T> to_kop(const LevelOp &op, double omega) {
   return k;
 }
 
-// Shortest band of a fused launch: coarse rows (pre kernel with restriction) or fine rows.
+// Shortest band of a fused launch with partial sums or over a batch (where the rows marched
+// beyond a band's own cost throughput): coarse rows (pre kernel with restriction) or fine rows.
 constexpr int kMinCoarseRows = 4, kMinFineRows = 8;
 
-// Rows of a pre launch and its bands.  grid.x (blocks across) is set by the caller; the
-// band height fills at most one round of resident blocks of the kernel fn.
-int pre_bands(const void *fn, int n, bool restrict_mode, dim3 *grid) {
-  const int rows_total = restrict_mode ? (n - 1) / 2 + 1 : n;
-  const int c = band_rows(rows_total, grid->x, resident_blocks(fn, kBlock, 0),
-                          restrict_mode ? kMinCoarseRows : kMinFineRows);
-  grid->y = cdiv(rows_total, c);
-  return c;
+// Rows per band.  A band of r rows marches unit r + extra row steps in whole turns of the
+// kernel's loop, so r fills its turns; the band with the fewest turns times rounds of
+// resident blocks, and of those the one with the least work in all.  Bands are a multiple of
+// `even` rows.  1025^2 FP64, two sweeps with defect and restriction: one round of bands of
+// four coarse rows (24 steps each, 774 blocks) 18.1 us, six (24 steps, 516 blocks) 16.4 us.
+int turn_rows(int total, int across, int capacity, int unit, int extra, int turn, int rmin, int even) {
+  int best = 0;
+  long cost0 = 0, work0 = 0;
+  for (int steps = turn;; steps += turn) {
+    const int r = (steps - extra) / unit / even * even;
+    if (steps <= extra || r < rmin) continue;
+    const long blocks = (long)across * cdiv(total, r);
+    const long cost = (blocks + capacity - 1) / capacity * steps, work = blocks * steps;
+    if (best == 0 || cost < cost0 || (cost == cost0 && work < work0)) {
+      best = r;
+      cost0 = cost;
+      work0 = work;
+    }
+    if (r >= total) return best;
+  }
 }
 
 template <typename T, int R, int NU, int MODE, bool RBS = false, bool XC = false>
 hipError_t pre_dispatch(PreArgs<T> args, dim3 grid, bool restrict_mode, int *nparts, hipStream_t s) {
   const void *fn = args.u != nullptr ? (const void *)k_pre2d<T, R, NU, MODE, true, RBS, XC>
                                      : (const void *)k_pre2d<T, R, NU, MODE, false, RBS, XC>;
-  args.chunk = pre_bands(fn, args.n, restrict_mode, &grid);
+  constexpr int K = NU + ((MODE & (kRestrict | kWriteR)) != 0 ? 1 : 0), LAG = R + 1;
+  constexpr int turn = (K - 1) * LAG + 1 <= 8 ? 8 : 16;  // the kernel's LR
+  const int total = restrict_mode ? (args.n - 1) / 2 + 1 : args.n;
+  const bool few = args.partials != nullptr || grid.z > 1;
+  args.chunk = turn_rows(total, grid.x, resident_blocks(fn, kBlock, 0), restrict_mode ? 2 : 1,
+                         (K - 1) * (R + LAG) + (restrict_mode ? 2 : 0), turn,
+                         few ? (restrict_mode ? kMinCoarseRows : kMinFineRows) : 2, 1);
+  grid.y = cdiv(total, args.chunk);
   if (nparts) *nparts = grid.x * grid.y;
   if (args.u != nullptr)
     hipLaunchKernelGGL((k_pre2d<T, R, NU, MODE, true, RBS, XC>), grid, dim3(kBlock), 0, s, args);
@@ -661,7 +707,9 @@ template <typename T, int R, int NU2, bool RBS = false, bool XC = false>
 hipError_t post_dispatch(int prolong, PostArgs<T> args, dim3 grid, hipStream_t s) {
   const void *fn = prolong == 3 ? (const void *)k_post2d<T, R, NU2, 3, RBS, XC>
                                 : (const void *)k_post2d<T, R, NU2, 1, RBS, XC>;
-  args.chunk = band_rows(args.n, grid.x, resident_blocks(fn, kBlock, 0), kMinFineRows);
+  constexpr int extra = NU2 * (2 * R + 1) + (NU2 * R) % 2;  // bands start on even rows
+  args.chunk = turn_rows(args.n, grid.x, resident_blocks(fn, kBlock, 0), 1, extra, kTurnPost,
+                         grid.z > 1 ? kMinFineRows : 2, 2);
   grid.y = cdiv(args.n, args.chunk);
   if (prolong == 3)
     hipLaunchKernelGGL((k_post2d<T, R, NU2, 3, RBS, XC>), grid, dim3(kBlock), 0, s, args);

@@ -20,6 +20,20 @@
 namespace mgk {
 namespace {
 
+// Threads per block.  A stage of a tile is a few hundred points and ends in a barrier, so
+// what a lone system on such a level waits for is the chain of passes one thread makes in
+// each stage: with 1024 threads that is one or two passes and not three to eight (solves
+// with 256 -> 1024 threads: 513^2 mixed 1148 -> 981 us, 1025^2 FP64 red-black 1335 -> 1080,
+// 2049^2 FP64 W cycle 11.77 -> 10.65 ms).  Where the launch has more blocks than the 256
+// compute units can hold a few of (batches), the other blocks cover those waits and many
+// small blocks are better: 48 served systems 14.5 ms with 256 threads, 16.7 with 1024.  The
+// line at 600 blocks was swept: 300 leaves the 561 blocks of a 513^2 level behind (1025^2
+// solve 1159 us against 1107), 1200 and 2400 change nothing for one system and cost the
+// batches 1 %, 5000 costs them 7 %.
+constexpr int kWide = 1024, kNarrow = 256;
+constexpr long kWideBlocks = 600;
+bool wide(const dim3 &g) { return (long)g.x * g.y * g.z <= kWideBlocks; }
+
 __device__ __forceinline__ bool stopped(const int *done) { return done != nullptr && *done != 0; }
 
 __device__ __forceinline__ int floordiv2(int a) { return a >= 0 ? a / 2 : -((1 - a) / 2); }
@@ -41,14 +55,22 @@ __device__ __forceinline__ T load_odd(const T *a, int x, int y, int n) {
   return T(s) * a[(size_t)yf * n + xf];
 }
 
-__device__ double block_sum(double v) {
-  __shared__ double ws[kBlock / 64];
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = v;
+// Sum over the block of acc[q], q < Q = kWide / TH: the addends of virtual thread
+// threadIdx.x + q TH of a block of kWide.  The same tree over kWide virtual threads for
+// every TH, so that a system's defect norm has the same bits alone and in a batch.
+template <int TH>
+__device__ double block_sum(const double (&acc)[kWide / TH]) {
+  __shared__ double ws[kWide / 64];
+#pragma unroll
+  for (int q = 0; q < kWide / TH; ++q) {
+    double v = acc[q];
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+    if ((threadIdx.x & 63) == 0) ws[q * (TH / 64) + (threadIdx.x >> 6)] = v;
+  }
   __syncthreads();
   double t = 0.0;
   if (threadIdx.x == 0)
-    for (int i = 0; i < kBlock / 64; ++i) t += ws[i];
+    for (int i = 0; i < kWide / 64; ++i) t += ws[i];
   return t;
 }
 
@@ -76,11 +98,11 @@ __device__ __forceinline__ T lu_at(const T *u, const T *sa, const T *sb, int p, 
 
 // Separable operator, first pass: A = sum_{k != 0} a_k (u(y+k) - u), B = sum_k b_k u(y+k)
 // at every point of rows [r0, r1) and columns [c0, c1) of the region.
-template <typename T, int R, int PW>
+template <typename T, int R, int PW, int TH>
 __device__ __forceinline__ void y_sums(const T *u, T *sa, T *sb, int r0, int r1, int c0, int c1,
                                        const KOp<T> &op) {
   const int w = c1 - c0;
-  for (int e = threadIdx.x; e < (r1 - r0) * w; e += kBlock) {
+  for (int e = threadIdx.x; e < (r1 - r0) * w; e += TH) {
     const int p = (r0 + e / w) * PW + c0 + e % w;
     const T c = u[p];
     T A = T(0), B = T(0);
@@ -101,12 +123,12 @@ __device__ __forceinline__ void y_sums(const T *u, T *sa, T *sb, int r0, int r1,
 // the coarse tile, (2CX+1) x (2CY+1) fine points.  Other modes: a TX x TY fine tile.
 constexpr int kCX = 16, kCY = 8, kTX = 32, kTY = 16;
 
-template <typename T, int R, int NU, int MODE, bool HAS_U>
-__global__ __launch_bounds__(kBlock) void k_pre_tile(const T *__restrict__ f, const T *__restrict__ u,
-                                                     T *__restrict__ uout, T *__restrict__ rout,
-                                                     T *__restrict__ fc, int n, KOp<T> op,
-                                                     double *__restrict__ partials,
-                                                     const int *__restrict__ done) {
+template <typename T, int R, int NU, int MODE, bool HAS_U, int TH>
+__global__ __launch_bounds__(TH) void k_pre_tile(const T *__restrict__ f, const T *__restrict__ u,
+                                                 T *__restrict__ uout, T *__restrict__ rout,
+                                                 T *__restrict__ fc, int n, KOp<T> op,
+                                                 double *__restrict__ partials,
+                                                 const int *__restrict__ done) {
   constexpr bool RESTRICT = (MODE & kPreRestrict) != 0;
   constexpr bool WRITE_R = (MODE & kPreWriteR) != 0;
   constexpr bool WRITE_U = (MODE & kPreWriteU) != 0;
@@ -137,44 +159,51 @@ __global__ __launch_bounds__(kBlock) void k_pre_tile(const T *__restrict__ f, co
   const int ox0 = RESTRICT ? 2 * I0 : DX0, oy0 = RESTRICT ? 2 * J0 : DY0;
   const int ox1 = min(ox0 + (RESTRICT ? 2 * kCX : kTX), n), oy1 = min(oy0 + (RESTRICT ? 2 * kCY : kTY), n);
 
-  for (int e = threadIdx.x; e < PS; e += kBlock) {
+  for (int e = threadIdx.x; e < PS; e += TH) {
     const int x = X0 + e % PW, y = Y0 + e / PW;
     sf[e] = load_odd(f, x, y, n);
     su[0][e] = HAS_U ? load_odd(u, x, y, n) : T(0);
   }
   __syncthreads();
 
-  double acc = 0.0;
+  double acc[kWide / TH] = {};
   // stage s (1..K) covers the loaded region less sR on every side; stage K the defect region
 #pragma unroll
   for (int s = 1; s <= K; ++s) {
     const int m = s * R;  // margin of stage s's region
     const T *ui = su[(s - 1) & 1];
     if constexpr (SEP) {
-      y_sums<T, R, PW>(ui, sy[0], sy[1], m, PH - m, m - R, PW - m + R, op);
+      y_sums<T, R, PW, TH>(ui, sy[0], sy[1], m, PH - m, m - R, PW - m + R, op);
       __syncthreads();
     }
     const int w = PW - 2 * m, h = PH - 2 * m;
-    for (int e = threadIdx.x; e < w * h; e += kBlock) {
+    auto point = [&](int e, double &sum) {
       const int i = m + e % w, j = m + e / w;
       const int p = j * PW + i;
       const T r = sf[p] - lu_at<T, R, PW>(ui, sy[0], sy[SEP ? 1 : 0], p, op);
       const int x = X0 + i, y = Y0 + j;
       if (s == 1 && partials != nullptr && x >= ox0 && x < ox1 && y >= oy0 && y < oy1 && x > 0 &&
           x < n - 1 && y > 0 && y < n - 1)
-        acc += (double)r * (double)r;
+        sum += (double)r * (double)r;
       if (s <= NU)
         su[s & 1][p] = ui[p] + stage_om(op, s, x + y) * r;
       else
         su[s & 1][p] = r;  // the defect (stage K of a residual mode)
+    };
+    for (int e = threadIdx.x; e < w * h; e += kWide) {
+#pragma unroll
+      for (int q = 0; q < kWide / TH; ++q)
+        if (q == 0 || e + q * TH < w * h) point(e + q * TH, acc[q]);
     }
     __syncthreads();
   }
   // outputs on the own fine points: the smoothed iterate (stage NU) and the defect
   const T *un = su[NU & 1];
   const T *rd = su[K & 1];
-  for (int e = threadIdx.x; e < (ox1 - ox0) * (oy1 - oy0); e += kBlock) {
-    const int x = ox0 + e % (ox1 - ox0), y = oy0 + e / (ox1 - ox0);
+  constexpr int OW = RESTRICT ? 2 * kCX : kTX, OH = RESTRICT ? 2 * kCY : kTY;  // own tile
+  for (int e = threadIdx.x; e < OW * OH; e += TH) {
+    const int x = ox0 + e % OW, y = oy0 + e / OW;
+    if (x >= ox1 || y >= oy1) continue;
     const int p = (y - Y0) * PW + (x - X0);
     const bool inside = x > 0 && x < n - 1 && y > 0 && y < n - 1;
     const size_t id = (size_t)y * n + x;
@@ -182,7 +211,7 @@ __global__ __launch_bounds__(kBlock) void k_pre_tile(const T *__restrict__ f, co
     if (WRITE_R) rout[id] = inside ? rd[p] : T(0);
   }
   if (RESTRICT) {
-    for (int e = threadIdx.x; e < kCX * kCY; e += kBlock) {
+    for (int e = threadIdx.x; e < kCX * kCY; e += TH) {
       const int I = I0 + e % kCX, J = J0 + e / kCX;
       if (I > nc - 1 || J > nc - 1) continue;
       T v = T(0);
@@ -198,7 +227,7 @@ __global__ __launch_bounds__(kBlock) void k_pre_tile(const T *__restrict__ f, co
     }
   }
   if (partials != nullptr) {
-    const double tot = block_sum(acc);
+    const double tot = block_sum<TH>(acc);
     if (threadIdx.x == 0) partials[blockIdx.y * gridDim.x + blockIdx.x] = tot;
   }
 }
@@ -206,10 +235,10 @@ __global__ __launch_bounds__(kBlock) void k_pre_tile(const T *__restrict__ f, co
 // ------------------------------------------------------------------------ post ----
 // A TX x TY fine tile: the corrected iterate on the tile plus an nu2 R halo, then nu2
 // sweeps over shrinking regions.
-template <typename T, int R, int NU2, int P>
-__global__ __launch_bounds__(kBlock) void k_post_tile(const T *__restrict__ v, const T *__restrict__ uin,
-                                                      const T *__restrict__ f, T *__restrict__ uout,
-                                                      int n, KOp<T> op, const int *__restrict__ done) {
+template <typename T, int R, int NU2, int P, int TH>
+__global__ __launch_bounds__(TH) void k_post_tile(const T *__restrict__ v, const T *__restrict__ uin,
+                                                  const T *__restrict__ f, T *__restrict__ uout,
+                                                  int n, KOp<T> op, const int *__restrict__ done) {
   constexpr int E = NU2 * R;
   constexpr int PW = kTX + 2 * E, PH = kTY + 2 * E, PS = PW * PH;
   constexpr int CW = PW / 2 + 5, CH = PH / 2 + 5, CS = CW * CH;  // coarse cover of the region
@@ -230,15 +259,15 @@ __global__ __launch_bounds__(kBlock) void k_post_tile(const T *__restrict__ v, c
   const int X0 = tx0 - E, Y0 = ty0 - E;
   const int C0 = floordiv2(X0) - 2, D0 = floordiv2(Y0) - 2;  // coarse cover origin
 
-  for (int e = threadIdx.x; e < CS; e += kBlock) sv[e] = load_odd(v, C0 + e % CW, D0 + e / CW, nc);
-  for (int e = threadIdx.x; e < PS; e += kBlock) {
+  for (int e = threadIdx.x; e < CS; e += TH) sv[e] = load_odd(v, C0 + e % CW, D0 + e / CW, nc);
+  for (int e = threadIdx.x; e < PS; e += TH) {
     const int x = X0 + e % PW, y = Y0 + e / PW;
     su[0][e] = load_odd(uin, x, y, n);
     if (NU2 > 0) sf[e] = load_odd(f, x, y, n);
   }
   __syncthreads();
   // stage 0: u + I_H^h v on the whole region
-  for (int e = threadIdx.x; e < PS; e += kBlock) {
+  for (int e = threadIdx.x; e < PS; e += TH) {
     const int x = X0 + e % PW, y = Y0 + e / PW;
     T wx[4], wy[4];
     auto weights = [](int fine, T (&w)[4]) {  // coarse fine/2-1 .. fine/2+2 (floor)
@@ -269,11 +298,11 @@ __global__ __launch_bounds__(kBlock) void k_post_tile(const T *__restrict__ v, c
     const int m = s * R;  // stage NU2 covers the tile
     const T *ui = su[(s - 1) & 1];
     if constexpr (SEP) {
-      y_sums<T, R, PW>(ui, sy[0], sy[SEP && NU2 > 0 ? 1 : 0], m, PH - m, m - R, PW - m + R, op);
+      y_sums<T, R, PW, TH>(ui, sy[0], sy[SEP && NU2 > 0 ? 1 : 0], m, PH - m, m - R, PW - m + R, op);
       __syncthreads();
     }
     const int w = PW - 2 * m, h = PH - 2 * m;
-    for (int e = threadIdx.x; e < w * h; e += kBlock) {
+    for (int e = threadIdx.x; e < w * h; e += TH) {
       const int i = m + e % w, j = m + e / w;
       const int p = j * PW + i;
       const T r = sf[NU2 > 0 ? p : 0] - lu_at<T, R, PW>(ui, sy[0], sy[SEP && NU2 > 0 ? 1 : 0], p, op);
@@ -282,9 +311,9 @@ __global__ __launch_bounds__(kBlock) void k_post_tile(const T *__restrict__ v, c
     __syncthreads();
   }
   const T *un = su[NU2 & 1];
-  const int w = min(kTX, n - tx0), h = min(kTY, n - ty0);
-  for (int e = threadIdx.x; e < w * h; e += kBlock) {
-    const int x = tx0 + e % w, y = ty0 + e / w;
+  for (int e = threadIdx.x; e < kTX * kTY; e += TH) {
+    const int x = tx0 + e % kTX, y = ty0 + e / kTX;
+    if (x >= n || y >= n) continue;
     const bool inside = x > 0 && x < n - 1 && y > 0 && y < n - 1;
     uout[(size_t)y * n + x] = inside ? un[(y - Y0) * PW + (x - X0)] : T(0);
   }
@@ -307,6 +336,17 @@ KOp<T> to_kop(const LevelOp &op, double omega) {
   return k;
 }
 
+template <typename T, int R, int NU, int MODE, int TH>
+void pre_tile_launch(const dim3 &grid, const T *f, const T *u, T *uout, T *rout, T *fc, int n,
+                     const KOp<T> &k, double *partials, const int *done, hipStream_t s) {
+  if (u != nullptr)
+    hipLaunchKernelGGL((k_pre_tile<T, R, NU, MODE, true, TH>), grid, dim3(TH), 0, s, f, u, uout, rout,
+                       fc, n, k, partials, done);
+  else
+    hipLaunchKernelGGL((k_pre_tile<T, R, NU, MODE, false, TH>), grid, dim3(TH), 0, s, f, u, uout, rout,
+                       fc, n, k, partials, done);
+}
+
 template <typename T, int R, int NU, int MODE>
 hipError_t pre_tile_dispatch(const T *f, const T *u, T *uout, T *rout, T *fc, int n, const KOp<T> &k,
                              double *partials, int *nparts, const int *done, hipStream_t s,
@@ -315,12 +355,10 @@ hipError_t pre_tile_dispatch(const T *f, const T *u, T *uout, T *rout, T *fc, in
   const int nc = (n - 1) / 2 + 1;
   const dim3 grid = RM ? dim3(cdiv(nc, kCX), cdiv(nc, kCY), slots) : dim3(cdiv(n, kTX), cdiv(n, kTY), slots);
   if (nparts) *nparts = grid.x * grid.y;
-  if (u != nullptr)
-    hipLaunchKernelGGL((k_pre_tile<T, R, NU, MODE, true>), grid, dim3(kBlock), 0, s, f, u, uout, rout,
-                       fc, n, k, partials, done);
+  if (wide(grid))
+    pre_tile_launch<T, R, NU, MODE, kWide>(grid, f, u, uout, rout, fc, n, k, partials, done, s);
   else
-    hipLaunchKernelGGL((k_pre_tile<T, R, NU, MODE, false>), grid, dim3(kBlock), 0, s, f, u, uout, rout,
-                       fc, n, k, partials, done);
+    pre_tile_launch<T, R, NU, MODE, kNarrow>(grid, f, u, uout, rout, fc, n, k, partials, done, s);
   return hipGetLastError();
 }
 
@@ -349,14 +387,25 @@ hipError_t pre_tile_r(int nu, int mode, const T *f, const T *u, T *uout, T *rout
   return hipErrorInvalidValue;
 }
 
+template <typename T, int R, int NU2, int P>
+void post_tile_launch(const dim3 &grid, const T *v, const T *uin, const T *f, T *uout, int n,
+                      const KOp<T> &k, const int *done, hipStream_t s) {
+  if (wide(grid))
+    hipLaunchKernelGGL((k_post_tile<T, R, NU2, P, kWide>), grid, dim3(kWide), 0, s, v, uin, f, uout, n, k,
+                       done);
+  else
+    hipLaunchKernelGGL((k_post_tile<T, R, NU2, P, kNarrow>), grid, dim3(kNarrow), 0, s, v, uin, f, uout, n,
+                       k, done);
+}
+
 template <typename T, int R, int NU2>
 hipError_t post_tile_dispatch(int prolong, const T *v, const T *uin, const T *f, T *uout, int n,
                               const KOp<T> &k, const int *done, hipStream_t s, int slots) {
   const dim3 grid(cdiv(n, kTX), cdiv(n, kTY), slots);
   if (prolong == 3)
-    hipLaunchKernelGGL((k_post_tile<T, R, NU2, 3>), grid, dim3(kBlock), 0, s, v, uin, f, uout, n, k, done);
+    post_tile_launch<T, R, NU2, 3>(grid, v, uin, f, uout, n, k, done, s);
   else
-    hipLaunchKernelGGL((k_post_tile<T, R, NU2, 1>), grid, dim3(kBlock), 0, s, v, uin, f, uout, n, k, done);
+    post_tile_launch<T, R, NU2, 1>(grid, v, uin, f, uout, n, k, done, s);
   return hipGetLastError();
 }
 

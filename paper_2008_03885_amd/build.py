@@ -9,7 +9,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libmgmi.so")
-SOURCES = ["kernels2d.hip", "fused2d.hip", "tile2d.hip", "tail.hip", "tail2d.hip", "kernels3d.hip", "runtime.hip",
+SOURCES = ["kernels2d.hip", "fused2d.hip", "tile2d.hip", "tail.hip", "tail2d.hip", "kernels3d.hip", "small3d.hip", "runtime.hip",
            "serve.hip", "rbc.hip", "rbc_passes.hip", "rbc_tail.hip", "noalloc.hip", "gs2d.hip", "restrict.hip", "tail3d.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -1279,13 +1279,21 @@ const void *sweep3d_fn(int mode, bool has_u, int xw, int ys = 1) {
                   : xsweep3d_fn<T, TO, 32>(mode, has_u);
 }
 
+// Levels of the direct kernels (small3d.hip): up to 65^3 all three of them win, at 129^3 the
+// marching kernels do (a 129^3 FP64 solve 3.77 ms with the line at 65; sweep, defect or
+// interpolation also at 129: 4.25, 3.87, 4.01 ms).  A forced shape of the marching kernel
+// (the variable var) keeps that kernel.
+constexpr int kSmallSide = 65;
+bool small_level(int n, const char *var) { return n <= kSmallSide && getenv(var) == nullptr; }
+
 }  // namespace
 
 int sweep_partials_3d(int n) {
   const long tiles = (long)cdiv(n, TX) * cdiv(n, TY);
   // the pencil sweep: 58 columns x 4 wavefronts of gpen_rows rows per block
   const long pencils = (long)cdiv(n, 58) * cdiv(n, 4 * std::min(gpen_rows<float>(), gpen_rows<double>()));
-  return (int)(std::max(tiles, pencils) * cdiv(n, kMinPlanes));
+  const int small = n <= kSmallSide ? small3d_partials(n) : 0;
+  return std::max((int)(std::max(tiles, pencils) * cdiv(n, kMinPlanes)), small);
 }
 
 // The sixth-order radius-3 cross runs the cross kernels with R = 3 (MG_X3_R3=0: the
@@ -1315,6 +1323,8 @@ hipError_t launch_sweep_3d(int mode, const LevelOp &op, double omega, const T *f
   // with R = 3 unless MG_X3_R3 = 0; every other operator the separable pencil kernel
   const bool xpath = op.cross || u == nullptr;
   const bool x3path = !xpath && op.cross3 && x3_r3();
+  if (op.cross && u != nullptr && mode != kSweepCorr && small_level(n, "MG_X3_W"))
+    return launch_small_sweep_3d<T, TO>(mode, op, omega, f, u, out, n, partials, nparts, done, s, colour);
   KOp<T> k = to_kop3<T>(op, omega);
   k.colour = colour;
   if (!xpath && !x3path) {
@@ -1462,6 +1472,7 @@ hipError_t launch_x2sweep_3d(const LevelOp &op, double omega, const T *f, const 
 hipError_t launch_sweep_corr_3d(const LevelOp &op, double omega, const float *f, const float *e,
                                 double *u64, int n, const int *done, hipStream_t s) {
   if (!op.cross || op.cross3) return hipErrorInvalidValue;
+  if (small_level(n, "MG_X3_W")) return launch_small_sweep_corr_3d(op, omega, f, e, u64, n, done, s);
   // the FP32 sweep's tiles: 128 x 16 points (two rows per thread) on the large levels
   const bool wide = wide_tiles<float>(n, "MG_X3_W");
   const int xw = wide ? (wide128() ? 128 : 64) : TX, ys = wide ? 2 : 1, nt = xw * TY;
@@ -1491,6 +1502,8 @@ hipError_t launch_resid_restrict_3d(const LevelOp &op, const T *f, const T *u, T
   const int nc = (n - 1) / 2 + 1;
   // the cross kernel also serves every operator on a zero u (the defect is f)
   if (op.cross || u == nullptr) {
+    if (small_level(n, "MG_XRR_TALL"))
+      return launch_small_resid_restrict_3d<T>(op, f, u, fc, n, done, s);
     // 16 x 3 coarse columns per 256-thread block on the small levels, 16 x 7 per 512
     // threads from 257^3 up (support 33 x 15, 90% of it owned; wider or larger tiles
     // measured slower).  MG_XRR_TALL = 0 or 1 forces the choice.
@@ -1546,6 +1559,7 @@ hipError_t launch_resid_restrict_3d(const LevelOp &op, const T *f, const T *u, T
 template <typename T>
 hipError_t launch_prolong_correct_3d(int prolong, const T *v, const T *uin, T *uout, int n,
                                      const int *done, hipStream_t s) {
+  if (small_level(n, "MG_P3_W")) return launch_small_prolong_3d<T>(prolong, v, uin, uout, n, done, s);
   const int xw = wide_tiles<T>(n, "MG_P3_W") ? 64 : TX, nt = xw * TY;
   // tiles cover points 1 .. n-1 (the kernel stores row and column 0)
   const int tiles = cdiv(n - 1, xw) * cdiv(n - 1, TY);

@@ -200,6 +200,22 @@ template <typename T>
 hipError_t launch_prolong_correct_3d(int prolong, const T *v, const T *uin, T *uout, int n,
                                      const int *done, hipStream_t s);
 
+// The same steps for the cross on a small level (small3d.hip); u != nullptr in the sweep,
+// out != u.  small3d_partials: partial sums of a sweep.
+int small3d_partials(int n);
+template <typename T, typename TO>
+hipError_t launch_small_sweep_3d(int mode, const LevelOp &op, double omega, const T *f, const T *u, TO *out,
+                                 int n, double *partials, int *nparts, const int *done, hipStream_t s,
+                                 int colour);
+hipError_t launch_small_sweep_corr_3d(const LevelOp &op, double omega, const float *f, const float *e,
+                                      double *u64, int n, const int *done, hipStream_t s);
+template <typename T>
+hipError_t launch_small_resid_restrict_3d(const LevelOp &op, const T *f, const T *u, T *fc, int n,
+                                          const int *done, hipStream_t s);
+template <typename T>
+hipError_t launch_small_prolong_3d(int prolong, const T *v, const T *uin, T *uout, int n, const int *done,
+                                   hipStream_t s);
+
 // ---- cubic-adjoint restriction (restrict.hip) --------------------------------------
 // fc = I_h^H r (appendix A.4, the 1/1024 operator) on the level (n-1)/2+1, r a fine defect
 // with zero boundary; every coarse point written (boundary zeros).  dim 2 or 3.

@@ -332,6 +332,7 @@ constexpr int kTail3Side = 17, kTail3Coarse = 9;
 struct Tail3Args {
   int nu1, nu2, prolong, zero_init, repeats;
   int rb;                // 1: red-black Jacobi sweeps, 0: omega-Jacobi
+  int cross;             // 1: the radius-2 cross (b the unit stencil)
   double om_d;           // omega / diagonal of the 17^3 operator
   double a[7], b[7];     // its 1D factors
   const double *dst;     // 9^3 sine table (7 x 7), then the 343 per-mode factors

@@ -471,6 +471,7 @@ hipError_t launch_tail_at(mg_ctx *c, int l, T *u, const T *f, bool zero_u, const
     a.zero_init = zero_u ? 1 : 0;
     a.repeats = repeats;
     a.rb = c->cfg.smoother == MG_SMOOTH_RBJ ? 1 : 0;
+    a.cross = c->ops[l].cross ? 1 : 0;
     a.om_d = c->omega / c->ops[l].diag;
     for (int k = 0; k < 7; ++k) {
       a.a[k] = c->ops[l].a[k];

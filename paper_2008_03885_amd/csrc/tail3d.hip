@@ -15,6 +15,15 @@
 // boundary planes and is odd across them), so every pass folds its indices instead of
 // keeping ghost frames.
 //
+// The radius-2 cross (b the unit stencil) takes one pass instead, with the x and y
+// neighbours from LDS and z in registers.
+//
+// One workgroup: the time is the chain of line passes and their barriers, and on entry the
+// wait for the level.  Issuing every load of the level and of the sine tables at once (they
+// were ten dependent turns of a loop) and the cross's own pass brought an FP64 V(2,1) visit
+// of a rediscretized level from 23.4 to 17.7 us, two Galerkin W(2,2) visits from 43.3 to
+// 41.5 us.  1024 threads in FP64 spill (257^3 Galerkin W(2,2) 12.1 ms, 512 threads 11.5 ms).
+//
 // The 9^3 level is solved exactly by sine transforms (FP64), as in the general tail.  One
 // launch runs the parent's gamma visits of the 17^3 level (repeats), each: nu1 sweeps,
 // defect and full weighting, the coarsest solve, interpolation and correction, nu2 sweeps.
@@ -48,8 +57,8 @@ __device__ __forceinline__ int fold_line(int p, int &s) {
 // (Q^3 each, interior points: BY and AY, then P2 and P1; the defect in g0), fc and uc
 // (NC^3 each, dense), then the coefficients a_1..a_3, b_0..b_3 and omega / diagonal.
 // The sine-transform work arrays (FP64) live in g1, which is free during the coarsest
-// solve.  Every array sits at a compile-time offset from the one base register.
-template <typename T>
+// solve; the sine table and the per-mode factors have a place of their own.  Every array sits at a compile-time offset from the one base register.
+template <typename T, bool CROSS>
 struct T3 {
   static constexpr int N = kT3N, Q = N - 2, NC = kT3NC, QC = NC - 2;
   static constexpr int NT = t3_threads<T>(), OPT = t3_outputs<T>(), WIN = OPT + 6;
@@ -58,10 +67,11 @@ struct T3 {
   static_assert(NTH <= NT, "a line pass fits the workgroup");
   static constexpr int OU = 0, OF = N * N * N, OG0 = 2 * N * N * N, OG1 = OG0 + Q * Q * Q,
                        OFC = OG1 + Q * Q * Q, OUC = OFC + NC * NC * NC, OCOEF = OUC + NC * NC * NC,
-                       TOTAL = OCOEF + 8;
+                       OSIN = (OCOEF + 9) / 2 * 2,  // doubles: sine table, then per-mode factors
+                       TOTAL = OSIN + (QC * QC + QC * QC * QC) * (int)(sizeof(double) / sizeof(T));
   // the sine-transform arrays start at the first 8-byte boundary in g1
   static constexpr int OG1D = (OG1 * (int)sizeof(T) + 7) / 8;
-  static_assert((OG1D + 2 * QC * QC * QC + QC * QC) * 8 <= OFC * (int)sizeof(T), "sine arrays fit in g1");
+  static_assert((OG1D + 2 * QC * QC * QC) * 8 <= OFC * (int)sizeof(T), "sine arrays fit in g1");
   T *base;
   const double *dst;  // global: the sine table, then the per-mode factors (2/N)^3 / lambda
   int nu1, nu2, prolong, rb;
@@ -73,6 +83,7 @@ struct T3 {
   __device__ T *fc() const { return base + OFC; }
   __device__ T *uc() const { return base + OUC; }
   __device__ T *coef() const { return base + OCOEF; }
+  __device__ double *sines() const { return reinterpret_cast<double *>(base + OSIN); }
   __device__ double *g1d() const { return reinterpret_cast<double *>(base) + OG1D; }
   __device__ static int di(int x, int y, int z) { return (z * N + y) * N + x; }
   __device__ static int ii(int x, int y, int z) { return ((z - 1) * Q + (y - 1)) * Q + (x - 1); }
@@ -207,7 +218,60 @@ struct T3 {
     }
     __syncthreads();
   }
+  // The radius-2 cross (b the unit stencil): a thread's outputs along z from a register
+  // window, the x and y neighbours from u.  One pass instead of three, and two barriers
+  // instead of four or five.
+  __device__ void pass_cross(int mode, int colour) const {
+    const int t = threadIdx.x;
+    T r[OPT], c[OPT];
+    int x = 0, y = 0, z0 = 0;
+    T *u = this->u();
+    if (t < NTH) {
+      const int line = t % LINES, part = t / LINES;
+      x = 1 + line % Q;
+      y = 1 + line / Q;
+      z0 = 1 + OPT * part;
+      const T *cf = coef(), *f = this->f() + di(x, y, 0);
+      const T a1 = cf[0], a2 = cf[1];
+      // the second neighbours in x and y: past the boundary the point itself, negated
+      const int om = x == 1 ? 0 : -2, op = x == Q ? 0 : 2, qm = y == 1 ? 0 : -2 * N, qp = y == Q ? 0 : 2 * N;
+      const T sm = x == 1 ? T(-1) : T(1), sp = x == Q ? T(-1) : T(1);
+      const T hm = y == 1 ? T(-1) : T(1), hp = y == Q ? T(-1) : T(1);
+      T w[WIN];
+      window<true>(u + di(x, y, 0), N * N, z0, w);
+#pragma unroll
+      for (int o = 0; o < OPT; ++o) {
+        const int z = min(z0 + o, Q);
+        const T *p = u + di(x, y, z);
+        c[o] = w[o + 3];
+        const T d1 = ((p[-1] - c[o]) + (p[1] - c[o])) + ((p[-N] - c[o]) + (p[N] - c[o])) +
+                     ((w[o + 2] - c[o]) + (w[o + 4] - c[o]));
+        const T d2 = ((sm * p[om] - c[o]) + (sp * p[op] - c[o])) + ((hm * p[qm] - c[o]) + (hp * p[qp] - c[o])) +
+                     ((w[o + 1] - c[o]) + (w[o + 5] - c[o]));
+        r[o] = f[z * N * N] - (a1 * d1 + a2 * d2);
+      }
+    }
+    if (mode == 0) __syncthreads();  // the update overwrites u, which others still read
+    if (t < NTH) {
+      T *g0 = this->g0();
+      const T om = coef()[7];
+#pragma unroll
+      for (int o = 0; o < OPT; ++o) {
+        const int z = z0 + o;
+        if (z > Q) break;
+        if (mode == 1)
+          g0[ii(x, y, z)] = r[o];
+        else
+          u[di(x, y, z)] = c[o] + ((colour == 0 || ((x + y + z) & 1) == (colour & 1)) ? om : T(0)) * r[o];
+      }
+    }
+    __syncthreads();
+  }
   __device__ void apply(int mode, int colour) const {
+    if constexpr (CROSS) {
+      pass_cross(mode, colour);
+      return;
+    }
     pass_y();
     pass_x();
     pass_z(mode, colour);
@@ -264,19 +328,20 @@ struct T3 {
     }
     __syncthreads();
   }
+  __device__ void load_sines() const {
+    double *s = sines();
+    for (int e = threadIdx.x; e < QC * QC + QC * QC * QC; e += NT) s[e] = dst[e];
+  }
   // uc = A_c^{-1} fc by sine transforms along x, y, z, a per-mode scaling, and back (FP64)
   __device__ void coarsest() const {
     constexpr int q = QC, m = QC * QC * QC;
-    double *a0 = g1d(), *a1 = a0 + m, *S = a1 + m;
+    double *a0 = g1d(), *a1 = a0 + m;
     const T *fc = this->fc();
     T *uc = this->uc();
-    const double *scale = dst + q * q;
-    for (int p = threadIdx.x; p < m; p += NT) {
-      const int X = 1 + p % q, Y = 1 + (p / q) % q, Z = 1 + p / (q * q);
-      a0[p] = (double)fc[(Z * NC + Y) * NC + X];
-    }
-    for (int e = threadIdx.x; e < q * q; e += NT) S[e] = dst[e];
-    __syncthreads();
+    const double *S = sines(), *scale = S + q * q;
+    auto dense = [](int p) {  // interior point p of the level in its dense array
+      return ((1 + p / (q * q)) * NC + 1 + (p / q) % q) * NC + 1 + p % q;
+    };
     auto pass = [&](const double *in, double *out, int stride, bool scaled) {
       for (int c = threadIdx.x; c < m; c += NT) {
         const int k = (c / stride) % q, b0 = c - k * stride;
@@ -287,15 +352,25 @@ struct T3 {
       }
       __syncthreads();
     };
-    pass(a0, a1, 1, false);
+    for (int c = threadIdx.x; c < m; c += NT) {  // the x pass, from the level's right-hand side
+      const int k = c % q;
+      const T *in = fc + dense(c - k);
+      double acc = 0.0;
+#pragma unroll
+      for (int i = 0; i < q; ++i) acc += S[k * q + i] * (double)in[i];
+      a1[c] = acc;
+    }
+    __syncthreads();
     pass(a1, a0, q, false);
     pass(a0, a1, q * q, true);
     pass(a1, a0, 1, false);
     pass(a0, a1, q, false);
-    pass(a1, a0, q * q, false);
-    for (int p = threadIdx.x; p < m; p += NT) {
-      const int X = 1 + p % q, Y = 1 + (p / q) % q, Z = 1 + p / (q * q);
-      uc[(Z * NC + Y) * NC + X] = (T)a0[p];
+    for (int c = threadIdx.x; c < m; c += NT) {  // the last z pass, into the level's iterate
+      const int k = c / (q * q), b0 = c - k * q * q;
+      double acc = 0.0;
+#pragma unroll
+      for (int i = 0; i < q; ++i) acc += S[k * q + i] * a1[b0 + i * q * q];
+      uc[dense(c)] = (T)acc;
     }
     __syncthreads();
   }
@@ -381,12 +456,12 @@ struct T3 {
   }
 };
 
-template <typename T>
+template <typename T, bool CROSS>
 __global__ __launch_bounds__(t3_threads<T>()) void k_tail3(Tail3Args a) {
   extern __shared__ __align__(16) unsigned char t3_lds[];
   const int *done = slot_done(a.done);
   if (done != nullptr && *done != 0) return;
-  using C = T3<T>;
+  using C = T3<T, CROSS>;
   constexpr int N = C::N, NC = C::NC;
   C c;
   c.base = reinterpret_cast<T *>(t3_lds);
@@ -402,12 +477,26 @@ __global__ __launch_bounds__(t3_threads<T>()) void k_tail3(Tail3Args a) {
   const size_t per = (size_t)N * N * N;
   const T *fg = slot_ptr(static_cast<const T *>(a.f_top), per);
   T *ug = slot_ptr(static_cast<T *>(a.u_top), per);
-  constexpr int NT = C::NT;
-  for (int i = threadIdx.x; i < N * N * N; i += NT) {
+  constexpr int NT = C::NT, NL = (N * N * N + NT - 1) / NT;
+  // every load of the level and of the sine tables is issued before the first is used
+  // (one after another they are ten waits on L2)
+  T fv[NL], uv[NL];
+#pragma unroll
+  for (int q = 0; q < NL; ++q) {
+    const int i = min(q * NT + (int)threadIdx.x, N * N * N - 1);
+    fv[q] = fg[i];
+    uv[q] = a.zero_init ? T(0) : ug[i];
+  }
+  c.load_sines();
+#pragma unroll
+  for (int q = 0; q < NL; ++q) {
+    const int i = q * NT + threadIdx.x;
     const int x = i % N, y = (i / N) % N, z = i / (N * N);
     const bool in = x > 0 && x < N - 1 && y > 0 && y < N - 1 && z > 0 && z < N - 1;
-    c.f()[i] = in ? fg[i] : T(0);
-    c.u()[i] = (a.zero_init || !in) ? T(0) : ug[i];
+    if (i < N * N * N) {
+      c.f()[i] = in ? fv[q] : T(0);
+      c.u()[i] = in ? uv[q] : T(0);
+    }
   }
   for (int i = threadIdx.x; i < NC * NC * NC; i += NT) {
     c.fc()[i] = T(0);
@@ -423,18 +512,24 @@ __global__ __launch_bounds__(t3_threads<T>()) void k_tail3(Tail3Args a) {
 static_assert(kT3N == 17 && kT3NC == 9 && kTail3Side == kT3N && kTail3Coarse == kT3NC, "tail sides");
 
 size_t tail3_lds_bytes(size_t es) {
-  return es == sizeof(float) ? T3<float>::TOTAL * sizeof(float) : T3<double>::TOTAL * sizeof(double);
+  return es == sizeof(float) ? T3<float, false>::TOTAL * sizeof(float) : T3<double, false>::TOTAL * sizeof(double);
 }
 
 template <typename T>
 hipError_t tail3_prepare() {
-  return hipFuncSetAttribute((const void *)k_tail3<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)tail3_lds_bytes(sizeof(T)));
+  const int bytes = (int)tail3_lds_bytes(sizeof(T));
+  const hipError_t e = hipFuncSetAttribute((const void *)k_tail3<T, true>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e != hipSuccess) return e;
+  return hipFuncSetAttribute((const void *)k_tail3<T, false>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
 template <typename T>
 hipError_t launch_tail3(const Tail3Args &args, hipStream_t s, int slots) {
-  hipLaunchKernelGGL((k_tail3<T>), dim3(1, 1, slots), dim3(t3_threads<T>()), tail3_lds_bytes(sizeof(T)), s, args);
+  const dim3 grid(1, 1, slots), block(t3_threads<T>());
+  if (args.cross)
+    hipLaunchKernelGGL((k_tail3<T, true>), grid, block, tail3_lds_bytes(sizeof(T)), s, args);
+  else
+    hipLaunchKernelGGL((k_tail3<T, false>), grid, block, tail3_lds_bytes(sizeof(T)), s, args);
   return hipGetLastError();
 }
 

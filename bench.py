@@ -51,21 +51,21 @@ WORKLOADS = {
 # dispatch, scaled by the counters of a plain copy of known size), valid only for the
 # kernel source they were taken on.
 MEASURED_TRAFFIC = {
-    # 4097^2 level 0, two sweeps + defect + full weighting: 172,251.9 KiB fetched x 2.0000
-    # + 169,196.7 KiB written x 1.0000 (a 2 GiB copy reads 1,048,595 KiB / writes 2,097,152)
-    "k_pre2d/f64/fused2d.hip/4097": {"bytes": 526022929, "source": "80797142e6561bc3"},
+    # 4097^2 level 0, two sweeps + defect + full weighting: 160,943.6 KiB fetched x 2.0000
+    # + 168,539.6 KiB written x 1.0000 (a 2 GiB copy reads 1,048,595 KiB / writes 2,097,152)
+    "k_pre2d/f64/fused2d.hip/4097": {"bytes": 502197043, "source": "8e0ad7e5812968a3"},
     # the same pass with red-black smoothing (one red-black sweep + defect + full weighting):
-    # 156,850.3 KiB x 2.0000 + 168,329.4 KiB x 1.0000
-    "k_pre2d/f64/fused2d.hip/4097/rb": {"bytes": 493592759, "source": "80797142e6561bc3"},
+    # 154,954.4 KiB x 2.0000 + 168,262.2 KiB x 1.0000
+    "k_pre2d/f64/fused2d.hip/4097/rb": {"bytes": 489647104, "source": "8e0ad7e5812968a3"},
     # 513^3 level 0 FP32 sweep (128 x 16 tiles from point 1, two rows per thread):
-    # 596,214.4 KiB x 2.0000 + 550,147.5 KiB x 1.0000
-    "k_xsweep3d/f32/kernels3d.hip/513": {"bytes": 1784398131, "source": "fbab958a857d17c1"},
+    # 596,325.5 KiB x 2.0000 + 550,977.3 KiB x 1.0000
+    "k_xsweep3d/f32/kernels3d.hip/513": {"bytes": 1785475379, "source": "c9cc66ac7eee2cf4"},
     # 1025^3 level 0 FP32 sweep (128 x 16 tiles from point 1, two rows per thread):
-    # 4,696,404.6 KiB x 2.0000 + 4,433,740.2 KiB x 1.0000
-    "k_xsweep3d/f32/kernels3d.hip/1025": {"bytes": 14158386586, "source": "fbab958a857d17c1"},
+    # 4,687,585.5 KiB x 2.0000 + 4,434,356.9 KiB x 1.0000
+    "k_xsweep3d/f32/kernels3d.hip/1025": {"bytes": 14140956570, "source": "c9cc66ac7eee2cf4"},
     # red-black coarsening, 4097^2 level-0 partial step (XCD-remapped 64 x 4 tiles):
-    # 131,353.0 KiB x 2.0000 + 131,137.3 KiB x 1.0000 (f is read whole: 24 B a point)
-    "k_rbc_smooth/f64/rbc.hip/4097": {"bytes": 403291537, "source": "b03ea673ddfdb24d"},
+    # 131,349.5 KiB x 2.0000 + 131,137.4 KiB x 1.0000 (f is read whole: 24 B a point)
+    "k_rbc_smooth/f64/rbc.hip/4097": {"bytes": 403288474, "source": "56214257cb9c7792"},
 }
 
 

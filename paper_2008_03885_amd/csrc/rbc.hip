@@ -681,6 +681,7 @@ struct mg_rbc_ctx {
   std::vector<double *> t2;       // second sweep target (an odd number of passes per visit)
   SolveState *state = nullptr;
   HostState *host = nullptr;      // pinned
+  bool unfinished = false;        // a solve's work may still be on the stream
   double *partial = nullptr, *norm_dev = nullptr, *norm_host = nullptr;
   double *ainv_t = nullptr;  // the coarsest operator's inverse, transposed (K x K)
   int *pos = nullptr;        // array index of each coarsest unknown
@@ -964,8 +965,11 @@ mg_status wait_checks(mg_rbc_ctx *h, int checks) {
 // once and leave u as it is.  4097^2 G1 V(1,1): the separate norm pass took 82 us and the
 // round trip to the host about 20 us of each 1.56 ms cycle.
 mg_status solve_async(mg_rbc_ctx *h, const double *f, double *u, int *cycles, double *hist) {
+  // the checks of a solve that ended in an error may still be on the stream
+  if (h->unfinished) RBC_HIP(hipStreamSynchronize(h->stream));
   h->host->checks = 0;
   h->host->done = 0;
+  h->unfinished = true;
   hipLaunchKernelGGL(k_rbc_start, dim3(1), dim3(1), 0, h->stream, h->state);
   RBC_HIP(hipGetLastError());
   int k = 0;
@@ -975,6 +979,7 @@ mg_status solve_async(mg_rbc_ctx *h, const double *f, double *u, int *cycles, do
     if (h->host->done) break;
   }
   RBC_HIP(hipStreamSynchronize(h->stream));
+  h->unfinished = false;
   if (cycles) *cycles = k;
   if (hist) std::memcpy(hist, h->host->hist, (size_t)(k + 1) * sizeof(double));
   const double r0 = h->host->hist[0], r = h->host->hist[k];

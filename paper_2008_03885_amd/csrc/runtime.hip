@@ -353,6 +353,7 @@ struct mg_ctx {
   DevState *mirror = nullptr;  // pinned host: the state as the checks leave it (checks last)
   hipEvent_t ev_async = nullptr;
   bool async_pending = false;
+  bool unfinished = false;     // a solve's work may still be on the stream
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
   const double *gf = nullptr;
@@ -935,9 +936,13 @@ mg_status begin_solve(mg_ctx *c, const double *f, double *u, double rtol, int ma
   if (!f || !u) return fail(MG_EINVAL, "null f or u");
   if (c->async_pending) return fail(MG_EBUSY, "an asynchronous solve is still pending");
   MG_HIP(hipSetDevice(c->device));
+  // the checks of a solve that ended in an error may still be on the stream, and would
+  // report to the mirror after it is cleared
+  if (c->unfinished) MG_HIP(hipStreamSynchronize(c->stream));
   mg_status st = ensure_graph(c, f, u);
   if (st != MG_OK) return st;
-  std::memset(c->mirror, 0, sizeof(DevState));  // no work of an earlier solve is left
+  std::memset(c->mirror, 0, sizeof(DevState));
+  c->unfinished = true;
   hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, c->stream, c->st, rtol, max_steps + 1,
                      floor_detect);
   MG_HIP(hipGetLastError());
@@ -980,6 +985,7 @@ void result_from_state(const mg_ctx *c, const DevState &hs, mg_result *res, mg_s
 // The finished solve's result: the stream has passed every step.
 mg_status fill_result(mg_ctx *c, mg_result *res, mg_status *outcome) {
   MG_HIP(hipStreamSynchronize(c->stream));
+  c->unfinished = false;
   result_from_state(c, *c->mirror, res, outcome);
   return MG_OK;
 }

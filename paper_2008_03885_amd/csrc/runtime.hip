@@ -358,7 +358,8 @@ struct mg_ctx {
   hipGraphExec_t gexec = nullptr;
   const double *gf = nullptr;
   double *gu = nullptr;
-  bool use_graph = true;
+  bool use_graph = true;   // steps are replayed as graphs (MG_GRAPH = 0: never)
+  int graph_above = 0, graph_above_async = 0;  // but those of at most this many launches
   bool fused = true;       // temporally blocked 2D kernels
   int tail_top = 0;        // first level handled by the LDS-resident tail (L: none)
   size_t tail_lds = 0;     // dynamic LDS bytes of the tail
@@ -896,7 +897,6 @@ hipError_t record_step(mg_ctx *c, const double *f, double *u, hipStream_t s) {
 }
 
 mg_status ensure_graph(mg_ctx *c, const double *f, double *u) {
-  if (!c->use_graph) return MG_OK;
   if (c->gexec && c->gf == f && c->gu == u) return MG_OK;
   if (c->gexec) {
     MG_HIP(hipGraphExecDestroy(c->gexec));
@@ -922,8 +922,8 @@ mg_status ensure_graph(mg_ctx *c, const double *f, double *u) {
   return MG_OK;
 }
 
-mg_status launch_step(mg_ctx *c, const double *f, double *u) {
-  if (c->use_graph) {
+mg_status launch_step(mg_ctx *c, const double *f, double *u, bool graph) {
+  if (graph) {
     MG_HIP(hipGraphLaunch(c->gexec, c->stream));
   } else {
     MG_HIP(record_step(c, f, u, c->stream));
@@ -931,16 +931,32 @@ mg_status launch_step(mg_ctx *c, const double *f, double *u) {
   return MG_OK;
 }
 
+// Kernel launches of one solve step, roughly.
+int step_launches(const mg_ctx *c) {
+  const bool rb = c->cfg.smoother != MG_SMOOTH_JACOBI;
+  int per = 2;  // a level visit: one pass before and one after the coarse correction
+  if (c->dim == 2 && c->fused && rb)
+    per = rb_passes(&c->cfg);
+  else if (c->dim == 3 || !c->fused)
+    per = (rb ? 2 : 1) * (c->cfg.nu1 + c->cfg.nu2) + 2;
+  long total = 0, visits = 1;
+  for (int l = 0; l < c->L && l < c->tail_top && total < 1000; ++l, visits *= c->cfg.gamma) total += visits * per;
+  total += std::max(1L, visits / c->cfg.gamma);  // the tail or the coarsest solve
+  return (int)std::min(1000L, total * (c->cfg.precision == MG_PREC_MIXED ? c->cfg.inner_cycles : 1) + 3);
+}
+
 mg_status begin_solve(mg_ctx *c, const double *f, double *u, double rtol, int max_steps,
-                      int floor_detect) {
+                      int floor_detect, bool graph) {
   if (!f || !u) return fail(MG_EINVAL, "null f or u");
   if (c->async_pending) return fail(MG_EBUSY, "an asynchronous solve is still pending");
   MG_HIP(hipSetDevice(c->device));
   // the checks of a solve that ended in an error may still be on the stream, and would
   // report to the mirror after it is cleared
   if (c->unfinished) MG_HIP(hipStreamSynchronize(c->stream));
-  mg_status st = ensure_graph(c, f, u);
-  if (st != MG_OK) return st;
+  if (graph) {
+    const mg_status st = ensure_graph(c, f, u);
+    if (st != MG_OK) return st;
+  }
   std::memset(c->mirror, 0, sizeof(DevState));
   c->unfinished = true;
   hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, c->stream, c->st, rtol, max_steps + 1,
@@ -1013,10 +1029,11 @@ mg_status wait_checks(mg_ctx *c, int checks) {
 // FP64 739 -> 563 us.
 mg_status run(mg_ctx *c, const double *f, double *u, double rtol, int max_steps, int floor_detect,
               mg_result *res) {
-  mg_status st = begin_solve(c, f, u, rtol, max_steps, floor_detect);
+  const bool graph = c->use_graph && step_launches(c) > c->graph_above;
+  mg_status st = begin_solve(c, f, u, rtol, max_steps, floor_detect, graph);
   if (st != MG_OK) return st;
   for (int k = 0; k <= max_steps; ++k) {
-    st = launch_step(c, f, u);
+    st = launch_step(c, f, u, graph);
     if (st == MG_OK) st = wait_checks(c, k + 1);
     if (st != MG_OK) return st;
     if (c->mirror->done != 0) break;
@@ -1029,20 +1046,6 @@ mg_status run(mg_ctx *c, const double *f, double *u, double rtol, int max_steps,
     g_error = res && res->floor_hit ? "solve stopped at the rounding floor above rtol"
                                     : "solve did not reach rtol";
   return outcome;
-}
-
-// Kernel launches of one solve step, roughly.
-int step_launches(const mg_ctx *c) {
-  const bool rb = c->cfg.smoother != MG_SMOOTH_JACOBI;
-  int per = 2;  // a level visit: one pass before and one after the coarse correction
-  if (c->dim == 2 && c->fused && rb)
-    per = rb_passes(&c->cfg);
-  else if (c->dim == 3 || !c->fused)
-    per = (rb ? 2 : 1) * (c->cfg.nu1 + c->cfg.nu2) + 2;
-  long total = 0, visits = 1;
-  for (int l = 0; l < c->L && l < c->tail_top && total < 1000; ++l, visits *= c->cfg.gamma) total += visits * per;
-  total += std::max(1L, visits / c->cfg.gamma);  // the tail or the coarsest solve
-  return (int)std::min(1000L, total * (c->cfg.precision == MG_PREC_MIXED ? c->cfg.inner_cycles : 1) + 3);
 }
 
 template <typename T>
@@ -1297,10 +1300,18 @@ mg_status setup_ctx(const mg_config *cfg, void *hip_stream, int slots, bool own_
   if (!own_top) {  // batches read their slots' states themselves
     if (hipHostMalloc((void **)&c->mirror, sizeof(DevState), hipHostMallocDefault) != hipSuccess)
       return bail(fail(MG_ENOMEM, "pinned host allocation failed"));
-    // Short steps are launched directly: a graph of a few kernels costs more than they do
-    // (65^2 FP64, 4 launches a step: 738 us as graphs, 614 direct; 65^3, 13: 2.50 and 2.39
-    // ms; 513^2 mixed, 31: 1.31 and 1.34 ms)
-    if (std::getenv("MG_GRAPH") == nullptr && step_launches(c) <= 16) c->use_graph = false;
+    // Short steps are launched directly.  In mg_solve the host launches step k + 1 while the
+    // rest of step k runs, and a graph of a few kernels costs more than they do.  Solve times,
+    // direct / graph, us: 65^2 (step_launches 4) 483 / 569, 257^2 (8) 642 / 730, 65^3 (14)
+    // 1470 / 1548, 4097^2 (16) 6218 / 6312; still 2870 / 3012 at 129^3 (19).  mg_solve_async
+    // enqueues max_cycles + 1 steps before it returns, so there the host's time counts too.
+    // The call, and until its work is done, for 101 steps, direct and graph, us: 65^2 (4)
+    // 1020, 1051 and 1770, 1782; 129^2 W (6) 1243, 1292 and 1755, 1866; 257^2 (8) 2075, 2112
+    // and 1890, 2105; 513^2 (10) 2853, 2889 and 2006, 2620; 4097^2 4465, 8059 and 1919, 8663.
+    if (std::getenv("MG_GRAPH") == nullptr) {
+      c->graph_above = 16;
+      c->graph_above_async = 6;
+    }
   }
   if (hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking) != hipSuccess)
     return bail(fail(MG_EDEVICE, "stream creation failed"));
@@ -1330,10 +1341,11 @@ mg_status mg_run_cycles(mg_handle h, const double *f, double *u, int ncycles, mg
 
 mg_status mg_solve_async(mg_handle h, const double *f, double *u) {
   if (!h) return fail(MG_EINVAL, "null handle");
-  mg_status st = begin_solve(h, f, u, h->cfg.rtol, h->cfg.max_cycles, 1);
+  const bool graph = h->use_graph && step_launches(h) > h->graph_above_async;
+  mg_status st = begin_solve(h, f, u, h->cfg.rtol, h->cfg.max_cycles, 1, graph);
   if (st != MG_OK) return st;
   for (int i = 0; i < h->cfg.max_cycles + 1; ++i) {
-    st = launch_step(h, f, u);
+    st = launch_step(h, f, u, graph);
     if (st != MG_OK) return st;
   }
   MG_HIP(hipEventRecord(h->ev_async, h->stream));
@@ -1645,7 +1657,7 @@ mg_status create(const mg_config *cfg, int slots, hipStream_t stream, mg_ctx **o
   mg_status st = setup_ctx(cfg, stream, slots, true, out);
   if (st != MG_OK) return st;
   mg_ctx *c = *out;
-  st = ensure_graph(c, (const double *)c->b64[0].f, (double *)c->b64[0].u);
+  st = c->use_graph ? ensure_graph(c, (const double *)c->b64[0].f, (double *)c->b64[0].u) : MG_OK;
   if (st != MG_OK) {
     mg_destroy(c);
     *out = nullptr;
@@ -1677,7 +1689,7 @@ mg_status admit(mg_ctx *c, int k, const double *f) {
 
 mg_status step(mg_ctx *c, int count) {
   for (int i = 0; i < count; ++i) {
-    mg_status st = launch_step(c, (const double *)c->b64[0].f, (double *)c->b64[0].u);
+    mg_status st = launch_step(c, (const double *)c->b64[0].f, (double *)c->b64[0].u, c->use_graph);
     if (st != MG_OK) return st;
   }
   return MG_OK;

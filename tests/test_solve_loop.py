@@ -83,3 +83,26 @@ st, k, hist = rbc.solve(h, F, U, 20)
 assert k == 5, (st, k)
 rbc.destroy(h)
 """)
+
+
+@pytest.mark.parametrize("n,sync_graph,async_graph", [(65, 0, 0), (129, 0, 0), (257, 0, 1), (4097, 0, 1)])
+def test_graphs_by_launches_of_a_step(fake, n, sync_graph, async_graph):
+    """A step of about 4, 6, 8 or 16 launches: mg_solve launches its kernels, and
+    mg_solve_async, which enqueues every step before it returns, replays a graph above 6."""
+    _run(fake, r"""
+n, sync_graph, async_graph = %d, %d, %d
+h = mg.mg_setup(mg.make_config(dim=2, n=n, max_cycles=20))
+fake.fake_stop_at(6)
+counts()
+st, res = mg.mg_solve(h, F, U)
+kernels, graphs = counts()
+assert st == mg.MG_OK and res.cycles == 5 and graphs == 6 * sync_graph, (st, res.cycles, graphs)
+mg.mg_solve_async(h, F, U)
+kernels, graphs = counts()
+assert graphs == 21 * async_graph and (kernels < 6) == bool(async_graph), (kernels, graphs)
+st, res = mg.mg_query(h)
+assert st == mg.MG_OK and res.cycles == 5, (st, res.cycles)
+st, res = mg.mg_solve(h, F, U)
+assert st == mg.MG_OK and res.cycles == 5, (st, res.cycles)
+mg.mg_destroy(h)
+""" % (n, sync_graph, async_graph))

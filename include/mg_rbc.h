@@ -87,7 +87,8 @@ mg_status mg_rbc_cycles(mg_rbc_ctx *h, const double *f, double *u, int ncycles);
 /* Cycles until the relative residual reaches rtol or max_cycles; blocks.  hist (host,
  * max_cycles + 1 entries, may be NULL) receives the residual norm before each cycle and
  * after the last; *cycles the number run.  MG_ENOCONV if rtol was not reached,
- * MG_ENUMERIC on a NaN or Inf norm. */
+ * MG_ENUMERIC on a NaN or Inf norm (a first norm that is Inf only because the squares of a
+ * finite residual overflow ends the solve with MG_OK and no cycle). */
 mg_status mg_rbc_solve(mg_rbc_ctx *h, const double *f, double *u, int *cycles, double *hist);
 
 /* sqrt(mean over the interior of (f - L_0 u)^2) into *out (host); blocks. */

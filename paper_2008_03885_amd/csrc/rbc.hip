@@ -469,17 +469,17 @@ __global__ __launch_bounds__(1024) void k_rbc_tail(TailArgs a) {
   }
 }
 
-// Per-block sums of the squared level-0 defect over the interior.
+// Per-block sums of the squared (magnitude: absolute) level-0 defect over the interior.
 __global__ __launch_bounds__(256) void k_rbc_resnorm(const double *__restrict__ f,
                                                      const double *__restrict__ u, int m, Op op,
-                                                     double *__restrict__ partial) {
+                                                     double *__restrict__ partial, bool magnitude) {
   __shared__ double red[256];
   double s = 0.0;
   // block b takes interior rows b + 1, b + 1 + gridDim.x, ...; its threads stride the row
   for (int i = 1 + blockIdx.x; i < m - 1; i += gridDim.x)
     for (int j = 1 + threadIdx.x; j < m - 1; j += blockDim.x) {
       const double r = f[(size_t)i * m + j] - apply_op(u, m, i, j, op);
-      s += r * r;
+      s += magnitude ? fabs(r) : r * r;
     }
   red[threadIdx.x] = s;
   __syncthreads();
@@ -890,11 +890,12 @@ mg_status cycle_passes(mg_rbc_ctx *h, int l, const double *f, double *u, bool ze
   return in == u ? MG_OK : fail(MG_EDEVICE, "sweep targets out of order");
 }
 
-// Partial sums of the squared residual of level 0; returns their number.
-int launch_norm(mg_rbc_ctx *h, const double *f, const double *u) {
+// Partial sums of the squared (magnitude: absolute) residual of level 0; returns their number.
+int launch_norm(mg_rbc_ctx *h, const double *f, const double *u, bool magnitude = false) {
   const Level &L = h->lv[0];
   const int blocks = std::min(kNormBlocks, L.m - 2);  // a block takes whole interior rows
-  hipLaunchKernelGGL(k_rbc_resnorm, dim3(blocks), dim3(256), 0, h->stream, f, u, L.m, L.op, h->partial);
+  hipLaunchKernelGGL(k_rbc_resnorm, dim3(blocks), dim3(256), 0, h->stream, f, u, L.m, L.op, h->partial,
+                     magnitude);
   return blocks;
 }
 
@@ -921,10 +922,10 @@ mg_status cycle(mg_rbc_ctx *h, int l, const double *f, double *u, bool zero, boo
   return MG_OK;
 }
 
-mg_status norm(mg_rbc_ctx *h, const double *f, const double *u, double *out) {
+mg_status norm(mg_rbc_ctx *h, const double *f, const double *u, double *out, bool magnitude = false) {
   const Level &L = h->lv[0];
   const size_t ni = (size_t)(L.m - 2) * (L.m - 2);
-  const int blocks = launch_norm(h, f, u);
+  const int blocks = launch_norm(h, f, u, magnitude);
   RBC_HIP(hipGetLastError());
   hipLaunchKernelGGL(k_rbc_sum, dim3(1), dim3(256), 0, h->stream, h->partial, blocks, 1.0 / (double)ni,
                      h->norm_dev);
@@ -933,6 +934,17 @@ mg_status norm(mg_rbc_ctx *h, const double *f, const double *u, double *out) {
   RBC_HIP(hipStreamSynchronize(h->stream));
   *out = *h->norm_host;
   return MG_OK;
+}
+
+mg_status not_finite() { return fail(MG_ENUMERIC, "residual norm is not finite"); }
+
+// A solve whose first norm r0 is not finite runs no cycle: no later norm is a decrease from
+// it.  MG_ENUMERIC if the residual itself is not finite, MG_OK if only its squares overflow.
+mg_status check_start(mg_rbc_ctx *h, const double *f, const double *u, double r0) {
+  if (std::isfinite(r0)) return MG_OK;
+  double mean = 0.0;
+  RBC_TRY(norm(h, f, u, &mean, true));
+  return std::isfinite(mean) ? MG_OK : not_finite();
 }
 
 // Whether every launch of a cycle takes the stopping flag (so that a solve can run ahead of
@@ -983,7 +995,8 @@ mg_status solve_async(mg_rbc_ctx *h, const double *f, double *u, int *cycles, do
   if (cycles) *cycles = k;
   if (hist) std::memcpy(hist, h->host->hist, (size_t)(k + 1) * sizeof(double));
   const double r0 = h->host->hist[0], r = h->host->hist[k];
-  if (k > 0 && !std::isfinite(r)) return fail(MG_ENUMERIC, "residual norm is not finite");
+  if (k == 0) RBC_TRY(check_start(h, f, u, r0));
+  if (k > 0 && !std::isfinite(r)) return not_finite();
   if (r > h->cfg.rtol * r0) return fail(MG_ENOCONV, "solve did not reach rtol");
   return MG_OK;
 }
@@ -1154,14 +1167,14 @@ mg_status mg_rbc_solve(mg_rbc_ctx *h, const double *f, double *u, int *cycles, d
   if (hist) hist[0] = r0;
   int k = 0;
   r = r0;
-  mg_status st = MG_OK;
-  while (r > h->cfg.rtol * r0 && k < h->cfg.max_cycles) {
+  mg_status st = check_start(h, f, u, r0);
+  while (st == MG_OK && r > h->cfg.rtol * r0 && k < h->cfg.max_cycles) {
     RBC_TRY(cycle(h, 0, f, u, false, false, nullptr));
     RBC_TRY(norm(h, f, u, &r));
     ++k;
     if (hist) hist[k] = r;
     if (!std::isfinite(r)) {
-      st = fail(MG_ENUMERIC, "residual norm is not finite");
+      st = not_finite();
       break;
     }
   }

@@ -290,14 +290,20 @@ hipError_t launch_small_sweep_3d(int mode, const LevelOp &op, double omega, cons
   const float rn = 1.0f / (float)n;
 #define MG_SS(MODE) \
   hipLaunchKernelGGL((k_ssweep3d<T, TO, MODE>), grid, dim3(kThreads), 0, s, f, u, out, n, rn, k, partials, done)
-  if (mode == kSweep) MG_SS(kSweep);
-  else if (mode == kSweepRB) MG_SS(kSweepRB);
-  else if (mode == kSweepZ2) MG_SS(kSweepZ2);
-  else if (mode == kResidual) MG_SS(kResidual);
-  else if (mode == kNormOnly) MG_SS(kNormOnly);
-  else return hipErrorInvalidValue;
+  if (mode == kResidual) {
+    MG_SS(kResidual);
+    return hipGetLastError();
+  }
+  if constexpr (std::is_same_v<T, TO>) {  // FP64 in, FP32 out: the defect of a refinement step only
+    if (mode == kSweep) MG_SS(kSweep);
+    else if (mode == kSweepRB) MG_SS(kSweepRB);
+    else if (mode == kSweepZ2) MG_SS(kSweepZ2);
+    else if (mode == kNormOnly) MG_SS(kNormOnly);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
 #undef MG_SS
-  return hipGetLastError();
 }
 
 hipError_t launch_small_sweep_corr_3d(const LevelOp &op, double omega, const float *f, const float *e,

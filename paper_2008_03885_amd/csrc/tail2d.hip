@@ -360,7 +360,7 @@ struct Engine {
   Lvl<T, 65, SEP> l65;
   Lvl<T, 33, SEP> l33;
   Lvl<T, 17, SEP> l17;
-  T *base65, *base33, *base17, *frame9;
+  T *frame9;
   T *xa, *xb;
   double *fvec;        // the 9^2 right-hand side, 49 values
   double inv[ENT];     // this thread's entries of the 9^2 inverse: row t / PARTS, columns t % PARTS + PARTS k
@@ -378,9 +378,8 @@ struct Engine {
   }
   // frame base of the level's other / current frame, uniform over threads
   template <int N>
-  __device__ __forceinline__ T *frame_of(const Lvl<T, N, SEP> &l, T *base, bool other) const {
+  __device__ __forceinline__ T *frame_of(const Lvl<T, N, SEP> &l, bool other) const {
     const int id = l.owner ? (l.y0 + 2) * Geo<N>::P + l.x + 2 : 2 * Geo<N>::P + 2;
-    (void)base;
     return (other ? l.oth : l.cur) - id;
   }
 
@@ -390,7 +389,7 @@ struct Engine {
       const int X = 1 + (t & 7), Y = 1 + (t >> 3);
       if (X <= kQ && Y <= kQ)
         fvec[(Y - 1) * kQ + X - 1] =
-            (double)full_weight<T, Geo<17>::P>(frame_of<17>(l17, base17, true) + origin<17>(), X, Y);
+            (double)full_weight<T, Geo<17>::P>(frame_of<17>(l17, true) + origin<17>(), X, Y);
     }
     __syncthreads();
     const int row = t / PARTS, p = t % PARTS;
@@ -433,10 +432,10 @@ struct Engine {
     l33.sweeps(o, a.nu1, a.rb, from, xa, xb);
     l33.store_defect(o, xa, xb);
     if (l17.act(0))
-      l17.f[0] = full_weight<T, Geo<33>::P>(frame_of<33>(l33, base33, true) + origin<33>(), l17.x, l17.y0);
+      l17.f[0] = full_weight<T, Geo<33>::P>(frame_of<33>(l33, true) + origin<33>(), l17.x, l17.y0);
     for (int g = 0; g < a.gamma; ++g) visit17(g == 0, 0);
     o = fetch<T, SEP>(op<33>());
-    l33.template prolong<Geo<17>::P>(frame_of<17>(l17, base17, false) + origin<17>(), a.prolong);
+    l33.template prolong<Geo<17>::P>(frame_of<17>(l17, false) + origin<17>(), a.prolong);
     l33.sweeps(o, a.nu2, a.rb, 0, xa, xb);
   }
   __device__ __forceinline__ void visit65(bool zero, int from) {
@@ -445,14 +444,14 @@ struct Engine {
     l65.sweeps(o, a.nu1, a.rb, from, xa, xb);
     l65.store_defect(o, xa, xb);
     if (l33.owner) {
-      const T *r = frame_of<65>(l65, base65, true) + origin<65>();
+      const T *r = frame_of<65>(l65, true) + origin<65>();
 #pragma unroll
       for (int k = 0; k < Lvl<T, 33, SEP>::ROWS; ++k)
         if (l33.act(k)) l33.f[k] = full_weight<T, Geo<65>::P>(r, l33.x, l33.y0 + k);
     }
     for (int g = 0; g < a.gamma; ++g) visit33(g == 0, 0);
     o = fetch<T, SEP>(op<65>());
-    l65.template prolong<Geo<33>::P>(frame_of<33>(l33, base33, false) + origin<33>(), a.prolong);
+    l65.template prolong<Geo<33>::P>(frame_of<33>(l33, false) + origin<33>(), a.prolong);
     l65.sweeps(o, a.nu2, a.rb, 0, xa, xb);
   }
 };
@@ -484,18 +483,15 @@ __device__ __forceinline__ void setup(Engine<T, TOP, SEP> &e, unsigned char *lds
   T *const frames = reinterpret_cast<T *>(e.fvec + 64);
   T *p = frames;
   if constexpr (TOP >= 65) {
-    e.base65 = p;
     Lvl<T, 65, SEP>::clear(p, p + Geo<65>::SZ, NT);
     e.l65.init(p, p + Geo<65>::SZ);
     p += 2 * Geo<65>::SZ;
   }
   if constexpr (TOP >= 33) {
-    e.base33 = p;
     Lvl<T, 33, SEP>::clear(p, p + Geo<33>::SZ, NT);
     e.l33.init(p, p + Geo<33>::SZ);
     p += 2 * Geo<33>::SZ;
   }
-  e.base17 = p;
   Lvl<T, 17, SEP>::clear(p, p + Geo<17>::SZ, NT);
   e.l17.init(p, p + Geo<17>::SZ);
   p += 2 * Geo<17>::SZ;

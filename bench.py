@@ -51,22 +51,23 @@ WORKLOADS = {
 # dispatch, scaled by the counters of a plain copy of known size), valid only for the
 # kernel source they were taken on.
 MEASURED_TRAFFIC = {
-    # 4097^2 level 0, two sweeps + defect + full weighting: 160,943.6 KiB fetched x 2.0000
-    # + 168,539.6 KiB written x 1.0000 (a 2 GiB copy reads 1,048,595 KiB / writes 2,097,152)
-    "k_pre2d/f64/fused2d.hip/4097": {"bytes": 502197043, "source": "8e0ad7e5812968a3"},
+    # 4097^2 level 0, two sweeps + defect + full weighting: 160,740.0 KiB fetched x 2.0000
+    # + 167,858.9 KiB written x 1.0000 (a 2 GiB copy reads 1,048,596 KiB / writes 2,097,152)
+    "k_pre2d/f64/fused2d.hip/4097": {"bytes": 501083034, "source": "06abcb7f0aa1a2be"},
     # the same pass with red-black smoothing (one red-black sweep + defect + full weighting):
-    # 154,954.4 KiB x 2.0000 + 168,262.2 KiB x 1.0000
-    "k_pre2d/f64/fused2d.hip/4097/rb": {"bytes": 489647104, "source": "8e0ad7e5812968a3"},
+    # 154,895.2 KiB x 2.0000 + 168,092.7 KiB x 1.0000
+    "k_pre2d/f64/fused2d.hip/4097/rb": {"bytes": 489352294, "source": "06abcb7f0aa1a2be"},
     # 513^3 level 0 FP32 sweep (128 x 16 tiles from point 1, two rows per thread):
-    # 596,325.5 KiB x 2.0000 + 550,977.3 KiB x 1.0000
-    "k_xsweep3d/f32/kernels3d.hip/513": {"bytes": 1785475379, "source": "c9cc66ac7eee2cf4"},
+    # 579,122.3 KiB x 2.0000 + 544,869.8 KiB x 1.0000
+    "k_xsweep3d/f32/kernels3d.hip/513": {"bytes": 1743989146, "source": "b4b0a92c340d43c8"},
     # 1025^3 level 0 FP32 sweep (128 x 16 tiles from point 1, two rows per thread):
-    # 4,687,585.5 KiB x 2.0000 + 4,434,356.9 KiB x 1.0000
-    "k_xsweep3d/f32/kernels3d.hip/1025": {"bytes": 14140956570, "source": "c9cc66ac7eee2cf4"},
-    # red-black coarsening, 4097^2 level-0 partial step (XCD-remapped 64 x 4 tiles):
-    # 131,349.5 KiB x 2.0000 + 131,137.4 KiB x 1.0000 (f is read whole: 24 B a point)
-    "k_rbc_smooth/f64/rbc.hip/4097": {"bytes": 403288474, "source": "56214257cb9c7792"},
+    # 4,682,429.9 KiB x 2.0000 + 4,424,715.1 KiB x 1.0000
+    "k_xsweep3d/f32/kernels3d.hip/1025": {"bytes": 14120524698, "source": "b4b0a92c340d43c8"},
+    # red-black coarsening, one 4097^2 G1 V(1,1) cycle, all its kernels:
+    # 708,243.9 KiB x 2.0000 + 669,297.3 KiB x 1.0000
+    "rbc_cycle/f64/4097": {"bytes": 2135843901, "source": "bd8cbc1b667a02f7"},
 }
+RBC_SOURCES = ("rbc_passes.hip", "rbc_tail.hip")  # the kernels of a red-black coarsening cycle
 
 
 def parse():
@@ -475,9 +476,38 @@ def pmc_probe(w, run, stream, level=0):
 
 
 
+def rbc_levels(n):
+    """The fewest red-black coarsening levels whose last one the coarsest solve takes."""
+    from paper_2008_03885_amd import rbc
+    def unknowns_of(l):  # of level l: interior points, only the even-index-sum ones if rotated
+        side = (n - 1) // 2 ** (l // 2) + 1
+        inner = (side - 2) ** 2
+        return inner if l % 2 == 0 else (inner + 1) // 2
+    levels = 2
+    while unknowns_of(levels - 1) > rbc.MG_RBC_MAX_COARSEST:
+        levels += 1
+    return levels
+
+
+def rbc_cycle_bytes(n, levels):
+    """Algorithmic bytes of one red-black coarsening V(1,1) cycle: per level above side 65 one
+    pass before the coarse correction (reads f, on level 0 also u; writes u and the coarse f)
+    and one after it (reads u, f and the coarse correction; writes u), the levels from side
+    65 down one read of f and one write of u."""
+    def side(l):
+        return (n - 1) // 2 ** (l // 2) + 1
+    def entries(l):
+        return side(l) * (side(l) if l % 2 == 0 else (side(l) + 1) // 2)
+    total, l = 0, 0
+    while l < levels - 1 and side(l) > 65:
+        total += 8 * ((3 if l == 0 else 2) * entries(l) + entries(l + 1)) + 8 * (3 * entries(l) + entries(l + 1))
+        l += 1
+    return total + 16 * entries(l)
+
+
 def rbc_pmc_probe(fd, stream, n):
-    """A plain copy of known size, then five level-0 red-black coarsening partial steps
-    (k_rbc_smooth), for hardware counters."""
+    """A plain copy of known size, then five red-black coarsening G1 V(1,1) cycles (the
+    benchmark's configuration), for hardware counters."""
     import torch
     from paper_2008_03885_amd import rbc
     a = torch.ones(256 * 1024 * 1024, device="cuda", dtype=torch.float64)  # 2 GiB
@@ -486,15 +516,13 @@ def rbc_pmc_probe(fd, stream, n):
         b.copy_(a)
     torch.cuda.synchronize()
     del a, b
-    h = rbc.setup(rbc.make_config(n=n, levels=20), stream.cuda_stream)
-    u = torch.rand_like(fd)
-    out = torch.empty_like(fd)
-    for _ in range(5):
-        rbc.kernel_smooth(h, 0, 1, fd.data_ptr(), u.data_ptr(), out.data_ptr())
+    h = rbc.setup(rbc.make_config(n=n, levels=rbc_levels(n)), stream.cuda_stream)
+    u = torch.zeros_like(fd)
+    rbc.cycles(h, fd.data_ptr(), u.data_ptr(), 5)
     torch.cuda.synchronize()
     rbc.destroy(h)
-    print(json.dumps({"copy_bytes_read": 2 << 30, "copy_bytes_written": 2 << 30,
-                      "kernel": "k_rbc_smooth", "launches": 5, "algorithmic_bytes": 20 * n * n}), flush=True)
+    print(json.dumps({"copy_bytes_read": 2 << 30, "copy_bytes_written": 2 << 30, "kernel": "k_rbc_*", "cycles": 5,
+                      "algorithmic_bytes_per_cycle": rbc_cycle_bytes(n, rbc_levels(n))}), flush=True)
 
 
 SERVE_BUDGET = 32 << 30
@@ -605,19 +633,12 @@ def rbc_bench(fd, stream, n, reps, cpu=True):
     """Red-black coarsening (section 4.3, 4.4) on the second-order five-point problem with
     the same right-hand side: V-cycles down to the first level of at most
     MG_RBC_MAX_COARSEST unknowns (17 levels at n = 4097, the last a 17x17 grid with 225
-    unknowns), solved from zero to 1e-10.  Also the level-0 partial step's
-    HBM rate (20 algorithmic bytes a point: u read and written, f read at half the points)
-    and the CPU oracle on a bounded sample."""
+    unknowns), solved from zero to 1e-10.  Also one cycle's HBM rate (rbc_cycle_bytes) and the
+    CPU oracle on a bounded sample."""
     import numpy as np
     import torch
     from paper_2008_03885_amd import rbc
-    def unknowns_of(l):  # of level l: interior points, only the even-index-sum ones if rotated
-        side = (n - 1) // 2 ** (l // 2) + 1
-        inner = (side - 2) ** 2
-        return inner if l % 2 == 0 else (inner + 1) // 2
-    levels = 2  # the fewest levels whose last one the coarsest solve takes
-    while unknowns_of(levels - 1) > rbc.MG_RBC_MAX_COARSEST:
-        levels += 1
+    levels = rbc_levels(n)
     unknowns = (n - 2) ** 2
     out = {"levels": levels, "problem": "second-order five-point operator, same right-hand side",
            "variants": {}}
@@ -641,20 +662,18 @@ def rbc_bench(fd, stream, n, reps, cpu=True):
         out["variants"][name] = {"ms": 1e3 * sec, "unknowns_per_s": unknowns / sec, "cycles": cyc,
                                  "rel_residual": hist[-1] / hist[0], "status": st}
         if (coarse, nu1, nu2, om) == RBC_VARIANTS[0]:
-            # cycles alone, HIP events on the handle's stream (the solve adds one norm a cycle)
+            # cycles alone, HIP events on the handle's stream (a solve's cycle also forms the
+            # norm, in its first pass)
             t = event_time(stream, lambda: rbc.cycles(h, fd.data_ptr(), ud.data_ptr(), 1), 10)
             out["cycle_ms"] = 1e3 * t
-            tmp = torch.empty_like(fd)
-            ps = event_time(stream, lambda: rbc.kernel_smooth(h, 0, 1, fd.data_ptr(), ud.data_ptr(),
-                                                              tmp.data_ptr()), 50)
-            byts = 20.0 * n * n
-            tr = MEASURED_TRAFFIC.get("k_rbc_smooth/f64/rbc.hip/%d" % n)
-            traffic = tr["bytes"] if tr and tr["source"] == source_hash("rbc.hip") else None
-            out["roofline"] = {"bound": "hbm", "kernel": "k_rbc_smooth level 0 (one partial step, FP64)",
-                               "achieved": byts / ps / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                               "frac": byts / ps / 1e9 / HBM_PEAK_GBS, "traffic": traffic,
-                               "avg_launch_us": ps * 1e6, "algorithmic_bytes_per_launch": byts}
-            del tmp
+            byts = rbc_cycle_bytes(n, levels)
+            tr = MEASURED_TRAFFIC.get("rbc_cycle/f64/%d" % n)
+            traffic = tr["bytes"] if tr and tr["source"] == source_hash(*RBC_SOURCES) else None
+            out["roofline"] = {"bound": "hbm", "kernel": "one G1 V(1,1) cycle (k_rbc_pre_*, k_rbc_post_*, "
+                                                         "k_rbc_tail_lds; FP64)",
+                               "achieved": byts / t / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                               "frac": byts / t / 1e9 / HBM_PEAK_GBS, "traffic": traffic,
+                               "cycle_us": t * 1e6, "algorithmic_bytes_per_cycle": byts}
         rbc.destroy(h)
     if cpu:
         from oracle import rbc as orbc

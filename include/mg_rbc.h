@@ -33,12 +33,14 @@
  *
  * Cycle (levels >= 2): nu1 red-black sweeps (omega-Jacobi on the F points, then on the C
  * points), the defect restricted with (1/8)[. 1 .; 1 4 1; . 1 .] onto the C points,
- * gamma cycles on the next level from a zero guess (on the last level one exact solve by
- * the inverse formed at set-up), the correction interpolated with (1/4)]. 1 .; 1 4 1; . 1 .[ (C points copy, F
- * points take the mean of their four C neighbours) and added, nu2 sweeps.  The levels of
- * side <= 33 (<= 65 where the last level is the standard 17^2 one; environment MG_RBC_TAIL:
- * another side, 0 for none) run in one workgroup launch per visit; above them each half of a level's visit is one pass (environment
- * MG_RBC_PASSES=0: separate launches per step), with the same arithmetic.
+ * gamma cycles on the next level from a zero guess (on the last level one exact solve), the
+ * correction interpolated with (1/4)]. 1 .; 1 4 1; . 1 .[ (C points copy, F points take the
+ * mean of their four C neighbours) and added, nu2 sweeps.  The levels of side <= 33 (<= 65
+ * where the last level is the standard 17^2 one; environment MG_RBC_TAIL: another side, 0 for
+ * none) run in one workgroup launch per visit; above them, with nu1 and nu2 both positive,
+ * each half of a level's visit is one pass (environment MG_RBC_PASSES=0: separate launches
+ * per step).  The exact solve applies the inverse formed at set-up, or, in the workgroup
+ * that ends at the standard 17^2 level, sine transforms.  These paths agree to rounding.
  *
  * Status codes and mg_last_error() are those of mg.h.  Every call is asynchronous on the
  * handle's stream unless it returns a host value.  Calls on one handle must not overlap.
@@ -72,7 +74,9 @@ typedef struct mg_rbc_config {
 typedef struct mg_rbc_ctx mg_rbc_ctx;
 
 /* Validates cfg (MG_EINVAL with a message), allocates the level arrays (MG_ENOMEM) on the
- * current device and binds the handle to `stream` (a hipStream_t, 0 = default). */
+ * current device and binds the handle to `stream` (a hipStream_t, 0 = default).  Each level
+ * holds three arrays (level 0 one), and one more from side 17 up where nu1 + max(1, nu2) is
+ * odd and nu1, nu2 are positive: 134 MB on level 0 at n = 4097. */
 mg_status mg_rbc_setup(const mg_rbc_config *cfg, void *stream, mg_rbc_ctx **out);
 void mg_rbc_destroy(mg_rbc_ctx *h);
 

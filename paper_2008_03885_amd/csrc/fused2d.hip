@@ -413,8 +413,9 @@ struct PostArgs {
 // pre kernel every carried value sits in a ring that the loop, unrolled by kTurnPost row
 // steps, addresses at compile time, so loads stay in flight; the first row step of a band is
 // on an even row.  (With queues shifted by a register move per row each step waited for the
-// loads of the step before.  Averages in a 4097^2 FP64 V(2,1) solve, both with their bands:
-// level 0 94 -> 97 us, at the traffic limit either way, 1025^2 12.6 -> 10.8 us.)
+// loads of the step before.  Averages of the working launches in 4097^2 FP64 V(2,1)
+// solves, both with their bands: level 0 105 -> 91 to 103 us by card, at the traffic limit
+// either way, 1025^2 13.0 -> 11.3 us.)
 constexpr int kTurnPost = 8;
 template <typename T, int R, int NU2, int P, bool RBS = false, bool XC = false>
 __global__ __launch_bounds__(kBlock) void k_post2d(PostArgs<T> a) {

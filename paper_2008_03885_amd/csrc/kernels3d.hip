@@ -1238,10 +1238,11 @@ inline bool wide128() {
 }
 
 // Rows per wavefront of the pencil sweep: 2 (FP32 126 VGPRs, four wavefronts per SIMD;
-// FP64 209), doubled for FP32 levels from 513^3 up.  Measured at 513^3: FP32 two rows
-// 571 us, four 540 us, but four rows lose on the smaller levels (257^3: 81 against
-// 94 us); FP64 one row (147 VGPRs) was slower than two in the whole solve (316 against
-// 308 ms).  MG_GPEN_ROWS = 1 or 2 sets the factor on every level.
+// FP64 209), doubled for FP32 levels from 513^3 up.  Measured with gpen_planes' bands:
+// 513^3 FP32 two rows 513 us, four 486 us, but four rows lose on the smaller levels (257^3:
+// 75 against 77 us; a 1025^3 Galerkin W(2,2) solve with four rows on every level 413 ms
+// against 402).  FP64 one row (147 VGPRs) was slower than two in the whole solve (316
+// against 308 ms, with the bands of before).  MG_GPEN_ROWS = 1 or 2 sets the factor on every level.
 template <typename T>
 constexpr int gpen_rows() { return 2; }
 template <typename T>

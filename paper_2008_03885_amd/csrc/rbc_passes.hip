@@ -16,10 +16,11 @@
 //
 // Bound: HBM on the large levels.  Measured (MI355X, kernel trace of a 4097^2 G1 V(1,1)
 // solve), against four partial steps of 92 us, a restriction of 117 us and an interpolation
-// of 93 us on level 0: pre 102 us (28 B a point, 4.6 TB/s; a 256 MB device copy runs at
-// 5.5 TB/s), post 110 us; rotated level 1 (8.4e6 points) pre from zero 42 us, post 61 us
-// (4 x 48, 84 and 42 us); a level of side 513 or less 6 to 8.5 us a pass, its launch and
-// the latency of one band.  Solve 14.0 -> 6.05 ms (257^2: 1.71 -> 1.17 ms).
+// of 93 us on level 0: pre 100 to 105 us by card (28 B a point, 4.5 TB/s; a 256 MB device copy
+// runs at 5.5 TB/s; 547 MB counted, 1.16x), post 102 to 113 us (561 MB counted); rotated
+// level 1 (8.4e6 points) pre from zero 45 us, post 57 to 59 us (4 x 48, 84 and 42 us); a level of side 513 or less
+// 4.5 to 8 us a pass, its launch and the latency of one band.  A cycle moves 1.22 times its
+// algorithmic bytes.  Solve 14.0 -> 6.05 ms (257^2: 1.71 -> 1.17 ms).
 #include <algorithm>
 
 #include "mg_internal.h"

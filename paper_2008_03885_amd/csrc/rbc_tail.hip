@@ -20,8 +20,8 @@
 // the sine modes): four passes over 225 values instead of a product with a 225 x 225
 // inverse streamed from L2 (12 us of the 35 us the general tail took from side 33).
 //
-// Measured (MI355X, kernel trace, G1 V(1,1)): 13.3 us a launch from side 65 with its 17^2
-// solve, in place of the general tail from side 33 (28 to 35 us) and four passes (27 us);
+// Measured (MI355X, kernel trace of solves, G1 V(1,1)): 14.5 us a launch from side 65 with its
+// 17^2 solve, in place of the general tail from side 33 (28 to 35 us) and four passes (27 us);
 // 257^2 solve 1171 -> 769 us, 4097^2 6.05 -> 5.57 ms.
 #include <cmath>
 #include <vector>

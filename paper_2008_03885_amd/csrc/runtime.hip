@@ -1255,8 +1255,9 @@ mg_status setup_ctx(const mg_config *cfg, void *hip_stream, int slots, bool own_
   if (hipMemcpy(c->ainv_t, inv.data(), inv.size() * sizeof(double), hipMemcpyHostToDevice) != hipSuccess)
     return bail(fail(MG_EDEVICE, "upload of the coarsest inverse failed"));
   {
-    // the tail solves the coarsest level by sine transforms unless MG_COARSE_DST=0 (or
-    // the operator fails the eigenpair check): no matrix to stream per visit
+    // the general and the 3D tail solve the coarsest level by sine transforms unless
+    // MG_COARSE_DST=0 (or the operator fails the eigenpair check): no matrix to stream per
+    // visit; the 2D tail of tail2d.hip holds the 9^2 inverse in registers
     const char *e = std::getenv("MG_COARSE_DST");
     const int q = c->ns[L - 1] - 2;
     const size_t tab_len = (size_t)q * q + (c->dim == 2 ? (size_t)q * q : (size_t)q * q * q);

@@ -8,8 +8,8 @@
 // threads of the level run at once and wait for one set of loads; the neighbours' lines
 // come from L1 and L2.
 //
-// Measured (FP64, from -> to, us): sweep 65^3 7.3 -> 5.3, 33^3 6.7 -> 4.4; defect and full
-// weighting 65^3 6.4 -> 6.2, 33^3 6.3 -> 4.6; interpolation 65^3 8.0 -> 5.6, 33^3 7.6 -> 4.7;
+// Measured (FP64, from -> to, us): sweep 65^3 7.3 -> 5.6, 33^3 6.7 -> 4.0; defect and full
+// weighting 65^3 6.4 -> 6.2, 33^3 6.3 -> 4.6; interpolation 65^3 8.0 -> 5.9, 33^3 7.6 -> 4.8;
 // a 65^3 V(2,1) solve 2328 -> 1840.
 //
 // The odd extension across the Dirichlet boundary (u(-i) = -u(i), boundary values zero) and

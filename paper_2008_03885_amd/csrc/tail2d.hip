@@ -22,7 +22,9 @@
 // from 33^2.  The general tail took 16-25 us from 33^2, 52 us for the two W visits from
 // 33^2 and 57 us separable red-black.  In clocks (2.1 GHz): a sweep over 65^2 3000 (FP32 1900),
 // over 33^2 1450, over 17^2 720, the 9^2 solve 1200 with its restriction, about 6000 for the
-// launch's first loads, LDS set-up and first instructions.  Solves: 2D 65^2 999 -> 739 us,
+// launch's first loads, LDS set-up and first instructions.  Inside solves (kernel trace, working
+// launches): FP64 V(2,1) from 65^2 17.0 us, FP32 10.2, the two visits of a W(2,1) cycle
+// 39.5, separable red-black from 33^2 15.9.  Solves: 2D 65^2 999 -> 739 us,
 // 2049^2 W(2,1) 28.4 -> 12.1 ms, 513^2 mixed 1.75 -> 1.31 ms.
 #include <cmath>
 #include <cstdint>

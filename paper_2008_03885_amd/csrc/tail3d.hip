@@ -22,7 +22,8 @@
 // wait for the level.  Issuing every load of the level and of the sine tables at once (they
 // were ten dependent turns of a loop) and the cross's own pass brought an FP64 V(2,1) visit
 // of a rediscretized level from 23.4 to 17.7 us, two Galerkin W(2,2) visits from 43.3 to
-// 41.5 us.  1024 threads in FP64 spill (257^3 Galerkin W(2,2) 12.1 ms, 512 threads 11.5 ms).
+// 41.5 us (averages over whole solves, whose last step's launches return at once; the
+// working ones now take 18.3 and 47.8 us, FP32 Galerkin 38.0).  1024 threads in FP64 spill (257^3 Galerkin W(2,2) 12.1 ms, 512 threads 11.5 ms).
 //
 // The 9^3 level is solved exactly by sine transforms (FP64), as in the general tail.  One
 // launch runs the parent's gamma visits of the 17^3 level (repeats), each: nu1 sweeps,
